@@ -73,7 +73,7 @@
  *
  * KIVI keys over the whole sequence (kivi_group = 0): when a key slice is
  * longer than one workgroup holds on chip, several co-resident workgroups
- * hold it together and exchange partial ranges through the caller's
+ * (more of them when there are few slices) hold it together and exchange partial ranges through the caller's
  * workspace, waiting for one another (a bounded number of polls); past 32
  * workgroups' rows, chunks of each slice merge their ranges into the same
  * workspace with atomics and a second launch writes the codes.  The

@@ -9,10 +9,11 @@
 //
 // Partitioned resident kernel (T at most 32 workgroups' capacity): a
 // persistent grid of 1024-thread workgroups, one per compute unit.  A group of
-// P workgroups (past 8, rounded up to 16 or 32, so that the groups fill every
-// compute unit) takes one key slice (l, b, h) at a time; workgroup q of the
-// group holds rows [q R, (q + 1) R) of the slice, every channel, on chip (9
-// row slots in LDS filled by buffer loads that write LDS directly, 15 in
+// P workgroups (1 to 8, 16 or 32: as many as hold the slice, or more where
+// few slices would leave compute units idle, see plan_k) takes one key slice
+// (l, b, h) at a time; workgroup q of the group holds rows [q R, (q + 1) R) of
+// the slice, every channel, on chip (15 row slots in registers and 9 in LDS,
+// filled by buffer loads that write LDS directly; shorter forms 15 or 8 in
 // registers), so each slice is read from HBM exactly once:
 //  1. per-channel min / max over the workgroup's rows, reduced across the
 //     rows a wavefront holds by shuffles and across wavefronts by LDS
@@ -224,9 +225,14 @@ __global__ __launch_bounds__(kSeqThreads) void kivi_seq_kernel(const Params p) {
 
 constexpr int kPartThreads = 1024;
 constexpr int kPartWaves = kPartThreads / 64;
-constexpr int kPartLdsSlots = 9;
-constexpr int kPartRegSlots = 15;
-constexpr int kPartSlots = kPartLdsSlots + kPartRegSlots;
+// Row slots of a workgroup, in registers and in LDS, by form (16 bytes a
+// thread and slot).  The longest form holds the most rows and streams whole
+// caches; the shorter ones have fewer loads to issue and wait for, for calls
+// whose slices are spread over more workgroups than would hold them.
+constexpr int kPartForms = 3;
+constexpr int kPartRegSlots[kPartForms] = {15, 15, 8};
+constexpr int kPartLdsSlots[kPartForms] = {9, 0, 0};
+constexpr int part_slots(int form) { return kPartRegSlots[form] + kPartLdsSlots[form]; }
 constexpr int kMaxPartners = 32;    // a group's partners share one XCD's 32 compute units
 constexpr int kSerialPartners = 8;  // up to this many, one thread per channel polls every partner
 // Exchange area (u64 words): a header (word 0 counts waits that ran out of
@@ -360,7 +366,7 @@ __device__ __forceinline__ void fold_partner(const uint64_t* w, uint32_t gen, fl
 // WIDE (more than kSerialPartners partners): every thread of the workgroup
 // polls partners; else one thread per channel polls them all (its own
 // instantiation, so the common case keeps the smaller register footprint).
-template <int D, int BITS, bool FAKE, bool WIDE>
+template <int D, int BITS, bool FAKE, bool WIDE, int FORM>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_t parts, uint32_t rows_per_part,
                       uint64_t* __restrict__ ex) {
@@ -369,7 +375,8 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   constexpr int LR = D / 8;                  // lanes per row (8 channels each)
   constexpr int RPW = 64 / LR;               // rows per wavefront per slot
   constexpr int RS = kPartWaves * RPW;       // rows per slot
-  __shared__ u32x4 rows_lds[kPartLdsSlots][kPartThreads];
+  constexpr int kRegSlots = kPartRegSlots[FORM], kLdsSlots = kPartLdsSlots[FORM];
+  __shared__ u32x4 rows_lds[kLdsSlots > 0 ? kLdsSlots : 1][kLdsSlots > 0 ? kPartThreads : 1];
   __shared__ float red[2 * D];               // per-channel min | max of the workgroup's rows
   __shared__ __attribute__((aligned(16))) uint32_t g_meta[D];
   __shared__ float g_inv[D];
@@ -412,7 +419,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     buffer_load16_lds(r, (lds_ptr)&rows_lds[j][wave * 64], src_off(j));
   };
 
-  u32x4 v[kPartRegSlots];
+  u32x4 v[kRegSlots];
   float mn[8], mx[8];
   // The odd channels (high halves) enter the range as the raw 32-bit words:
   // finite BF16 high halves with any low bits order exactly as the BF16
@@ -438,19 +445,19 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       mx[e] = -__builtin_inff();
     }
 #pragma unroll
-    for (int k = 0; k < kPartRegSlots; ++k) range8(v[k]);
+    for (int k = 0; k < kRegSlots; ++k) range8(v[k]);
     __builtin_amdgcn_s_waitcnt(kWaitVmem0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < kPartLdsSlots; ++j) range8(rows_lds[j][tid]);
+    for (int j = 0; j < kLdsSlots; ++j) range8(rows_lds[j][tid]);
   };
 
   {
     const __amdgpu_buffer_rsrc_t r = slice_rsrc(cur.s);
 #pragma unroll
-    for (int j = 0; j < kPartLdsSlots; ++j) load_lds(r, j);
+    for (int j = 0; j < kLdsSlots; ++j) load_lds(r, j);
 #pragma unroll
-    for (int k = 0; k < kPartRegSlots; ++k) v[k] = load_reg(r, kPartLdsSlots + k);
+    for (int k = 0; k < kRegSlots; ++k) v[k] = load_reg(r, kLdsSlots + k);
   }
   range_pass();
 
@@ -582,13 +589,13 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     auto code_pass = [&](bool refill) {
       const __amdgpu_buffer_rsrc_t r = slice_rsrc(nxt.s);
 #pragma unroll
-      for (int k = 0; k < kPartRegSlots; ++k) {
-        emit(v[k], kPartLdsSlots + k);
+      for (int k = 0; k < kRegSlots; ++k) {
+        emit(v[k], kLdsSlots + k);
         __builtin_amdgcn_sched_barrier(0);
-        if (refill) v[k] = load_reg(r, kPartLdsSlots + k);
+        if (refill) v[k] = load_reg(r, kLdsSlots + k);
       }
 #pragma unroll
-      for (int j = 0; j < kPartLdsSlots; ++j) {
+      for (int j = 0; j < kLdsSlots; ++j) {
         emit(rows_lds[j][tid], j);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -596,7 +603,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         __builtin_amdgcn_s_waitcnt(kWaitLds0);  // every slot read before it is refilled
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < kPartLdsSlots; ++j) load_lds(r, j);
+        for (int j = 0; j < kLdsSlots; ++j) load_lds(r, j);
       }
     };
     if (!nxt.valid) {
@@ -721,9 +728,9 @@ __global__ void zero_words_kernel(uint64_t* w, uint32_t n) {
 
 // ---------------------------------------------------------------- host side
 
-int kivi_part_capacity(int D) { return kPartSlots * kPartWaves * (512 / D); }
+int kivi_part_capacity(int D, int form = 0) { return part_slots(form) * kPartWaves * (512 / D); }
 
-// Workgroups per slice of the resident kernel, 0 for the split kernels.  A
+// Fewest workgroups per slice of the resident kernel, 0 for the split kernels.  A
 // grid holds 8 groups per 8 P workgroups, so past 8 partners P is rounded up
 // to 16 or 32, which fill every compute unit; each partner keeps at least one
 // row ((P - 1) ceil(T / P) < T holds for T > (P - 1)^2).
@@ -768,6 +775,7 @@ struct KiviPlan {
   bool resident = false;
   bool split = false;
   int parts = 0;
+  int form = 0;
   uint32_t n_items = 0, groups = 0, rows_per_part = 0;
   uint32_t clear_words = 0;
 };
@@ -780,33 +788,59 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   int cus = 0;
   hipError_t e = grid_cus(&cus);
   if (e != hipSuccess) return e;
-  const int parts = kivi_partners(p.T, D);
-  if (parts > 0 && (parts == 1 || has_ws)) {
-    int per_cu = 0;
-    e = parts > kSerialPartners
-            ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kivi_part_kernel<D, BITS, FAKE, true>, kPartThreads, 0)
-            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kivi_part_kernel<D, BITS, FAKE, false>, kPartThreads,
-                                                           0);
-    if (e != hipSuccess) return e;
-    const uint32_t resident = (uint32_t)std::max(per_cu, 0) * (uint32_t)cus;  // workgroups held at once
-    uint32_t cap = resident / (uint32_t)parts;
-    if (parts > 1) cap = std::min(cap, (uint32_t)(kExMaxWgs / parts));
-    cap = cap / 8u * 8u;
-    const uint32_t rows_per_part = (uint32_t)((p.T + parts - 1) / parts);
-    if (cap > 0 && rows_per_part <= (uint32_t)kivi_part_capacity(D)) {  // every row fits a slot
-      pl->resident = true;
-      pl->parts = parts;
-      pl->groups = std::min((pl->n_items + 7u) / 8u * 8u, cap);
-      pl->rows_per_part = rows_per_part;
-      if (parts > 1) pl->clear_words = (uint32_t)(kExHeader + (uint64_t)pl->groups * 2 * parts * D);
-      return hipSuccess;
+  const int fewest = kivi_partners(p.T, D);
+  if (fewest > 0 && (fewest == 1 || has_ws)) {
+    // Workgroups per slice and form, by the time of the call in twentieths of
+    // a full slot: a round (one slice per group) takes its used slots, a third
+    // of the empty ones (they load the last row again) and the exchange, three.
+    // Measured (2-bit keys at head_dim 128, T = 3000, whole calls, one box):
+    // 28 slices in place, 2 workgroups of the longest form 30.1 us, 8 of it
+    // 30.3, 6 of the shortest 21.6; 56 slices, 2 of the longest 35.0, 4 of the
+    // middle one 31.2, 6 of the shortest (two rounds) 34.3; 280 slices, 2 of
+    // the longest 111.6, 4 of the middle one 113.2, 6 of the shortest 115.5;
+    // 3584 slices (3 bits) 1346, 1400 and 1501.  Shorter forms are therefore
+    // taken for one round, or when they hold the slice in the fewest
+    // workgroups.
+    uint64_t best = ~0ull;
+    for (int form = 0; form < kPartForms; ++form) {
+      for (int parts = fewest; parts <= (has_ws ? kMaxPartners : 1); parts += parts < kSerialPartners ? 1 : parts) {
+        // groups held at once, one workgroup per compute unit (its registers
+        // and, in the longest form, its LDS admit one)
+        uint32_t cap = (uint32_t)cus / (uint32_t)parts;
+        if (parts > 1) cap = std::min(cap, (uint32_t)(kExMaxWgs / parts));
+        cap = cap / 8u * 8u;
+        const uint32_t rows = (uint32_t)((p.T + parts - 1) / parts);
+        if (cap == 0 || rows > (uint32_t)kivi_part_capacity(D, form)) continue;  // every row fits a slot
+        if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;             // every partner has a row
+        const uint32_t groups = std::min((pl->n_items + 7u) / 8u * 8u, cap);
+        const uint32_t rounds = (pl->n_items + groups - 1) / groups;
+        if (form > 0 && rounds > 1 && parts > fewest) continue;
+        const uint32_t per_slot = (uint32_t)(kPartWaves * (512 / D));
+        const uint32_t used = (rows + per_slot - 1) / per_slot;
+        const uint64_t cost = (uint64_t)rounds * (20u * used + 7u * ((uint32_t)part_slots(form) - used) + 60u);
+        if (cost >= best) continue;
+        best = cost;
+        pl->resident = true;
+        pl->form = form;
+        pl->parts = parts;
+        pl->groups = groups;
+        pl->rows_per_part = rows;
+        pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * 2 * parts * D) : 0;
+      }
     }
+    if (pl->resident) return hipSuccess;
   }
   if (has_ws) {
     pl->split = true;
     pl->clear_words = (uint32_t)(kExHeader + (uint64_t)std::min(pl->n_items, kSplitBatch) * D);
   }
   return hipSuccess;
+}
+
+template <int D, int BITS, bool FAKE, bool WIDE, int FORM>
+static void launch_part(const Params& p, const KiviPlan& pl, void* ws, dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, WIDE, FORM>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
+                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part, (uint64_t*)ws);
 }
 
 template <int D, int BITS, bool FAKE>
@@ -822,12 +856,16 @@ static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t 
   }
   if (pl.resident) {
     const dim3 grid(pl.groups * (uint32_t)pl.parts);
-    if (pl.parts > kSerialPartners)
-      hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, true>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
-                         pl.groups, (uint32_t)pl.parts, pl.rows_per_part, (uint64_t*)ws);
+    const bool wide = pl.parts > kSerialPartners;
+    if (pl.form == 0)
+      wide ? launch_part<D, BITS, FAKE, true, 0>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, false, 0>(p, pl, ws, grid, stream);
+    else if (pl.form == 1)
+      wide ? launch_part<D, BITS, FAKE, true, 1>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, false, 1>(p, pl, ws, grid, stream);
     else
-      hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, false>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
-                         pl.groups, (uint32_t)pl.parts, pl.rows_per_part, (uint64_t*)ws);
+      wide ? launch_part<D, BITS, FAKE, true, 2>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, false, 2>(p, pl, ws, grid, stream);
     return hipGetLastError();
   }
   if (pl.split) {

@@ -179,6 +179,30 @@ def test_capacity_boundary(D, T, img_len, img_start):
     _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), f"D{D}-T{T}-n{img_len}-s{img_start}")
 
 
+# The resident kernel's forms (24, 15 and 8 slots of 8192/D rows) at their
+# capacities, one row past them and just below: one round of a short form over
+# more workgroups than the slice needs, the longest form at the capacity of 8
+# workgroups on a grid that holds no more, and several rounds on a small grid.
+def _form_cases():
+    out = []
+    for D in (64, 128, 256):
+        r = 8192 // D
+        for cus, P, slots in (("256", 6, 8), ("256", 4, 15), ("256", 32, 8), ("64", 8, 24), ("48", 2, 24)):
+            out += [(D, cus, P * slots * r + d) for d in (-3, 0, 1) if P * slots * r + d > 24 * r]
+    return out
+
+
+@pytest.mark.parametrize("D,cus,T", _form_cases(), ids=lambda v: str(v))
+def test_form_boundary(D, cus, T, monkeypatch):
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    w = small("kivi", D, 2, 1, img_len=T - 9, img_start=4, text=5, L=2, B=3, H=5,
+              n_protected=2).with_(kivi_group=0)
+    K, V = synthkv.gen_kv(w)
+    K[0, :, :, T - 1, 5] = -4000.0  # extremes in the last and first rows
+    K[0, :, :, 0, 9] = 5000.0
+    _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), f"D{D}-T{T}-cus{cus}")
+
+
 @pytest.mark.parametrize("T", [1536, 1537, 3008, 12288, 12289, 24577, 49152, 49153])
 @pytest.mark.parametrize("inplace", [False, True])
 def test_capacity_boundary_fake(T, inplace):
