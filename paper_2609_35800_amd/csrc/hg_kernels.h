@@ -110,7 +110,8 @@ hipError_t launch_fake_quantize(const Params& p, int base, int D, int bits, bool
 // earlier launch of the call (else the launch clears them itself).
 hipError_t launch_kivi_seq(const Params& p, int D, int bits, bool fake, void* ws, bool cleared, hipStream_t stream);
 hipError_t kivi_seq_clear_words(const Params& p, int D, int bits, bool fake, void* ws, uint32_t* words);
-// Workgroups per slice of the resident kernel (0: the split kernels), and
+// Fewest workgroups of the resident kernel that hold a slice (0: the split
+// kernels), and
 // the exchange workspace bytes a call with T rows per slice needs (0: none).
 int kivi_partners(int T, int D);
 uint64_t kivi_workspace_bytes(int T, int D);

@@ -9,12 +9,14 @@
 //
 // Partitioned resident kernel (T at most 32 workgroups' capacity): a
 // persistent grid of 1024-thread workgroups, one per compute unit.  A group of
-// P workgroups (1 to 8, 16 or 32: as many as hold the slice, or more where
+// P workgroups (1 to 8, 16 or 32: as many as hold the slice, or up to 8 where
 // few slices would leave compute units idle, see plan_k) takes one key slice
 // (l, b, h) at a time; workgroup q of the group holds rows [q R, (q + 1) R) of
 // the slice, every channel, on chip (15 row slots in registers and 9 in LDS,
 // filled by buffer loads that write LDS directly; shorter forms 15 or 8 in
-// registers), so each slice is read from HBM exactly once:
+// registers), so each slice is read from HBM exactly once.  (A second read
+// costs as much as the first wherever it is served from: reads run at 7.1-7.3
+// TB/s from HBM and from the Infinity Cache alike.)
 //  1. per-channel min / max over the workgroup's rows, reduced across the
 //     rows a wavefront holds by shuffles and across wavefronts by LDS
 //     atomics;
@@ -227,8 +229,9 @@ constexpr int kPartThreads = 1024;
 constexpr int kPartWaves = kPartThreads / 64;
 // Row slots of a workgroup, in registers and in LDS, by form (16 bytes a
 // thread and slot).  The longest form holds the most rows and streams whole
-// caches; the shorter ones have fewer loads to issue and wait for, for calls
-// whose slices are spread over more workgroups than would hold them.
+// caches; the shorter ones issue and wait for fewer loads where a workgroup
+// has fewer rows (testing each slot's use instead made every wait a full one,
+// 1346 -> 1440 us on 3584 slices of 3008 rows).
 constexpr int kPartForms = 3;
 constexpr int kPartRegSlots[kPartForms] = {15, 15, 8};
 constexpr int kPartLdsSlots[kPartForms] = {9, 0, 0};
@@ -363,6 +366,43 @@ __device__ __forceinline__ void fold_partner(const uint64_t* w, uint32_t gen, fl
   b = fmaxf(b, __uint_as_float((uint32_t)v & 0xFFFF0000u));
 }
 
+// The same for partners first, first + step, ... (below parts, without q):
+// `w` is partner 0's word of the channel, the partners' words stride words
+// apart.  The words of N partners are loaded together, so they cost one round
+// trip (28 slices of 8 workgroups in place 23.3 -> 21.9 us).
+template <int N>
+__device__ __forceinline__ void fold_partners(const uint64_t* w, uint32_t stride, uint32_t first, uint32_t step,
+                                              uint32_t parts, uint32_t q, uint32_t gen, float& a, float& b,
+                                              uint32_t& timeouts) {
+  for (uint32_t r0 = first; r0 < parts; r0 += N * step) {
+    uint64_t v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const uint32_t r = min(r0 + k * step, parts - 1);
+      v[k] = __hip_atomic_load(w + (size_t)r * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const uint32_t r = r0 + k * step;
+      if (r >= parts || r == q) continue;
+      uint64_t x = v[k];
+      uint32_t spin = 0;
+      while ((uint32_t)(x >> 32) != gen && spin < kSpinLimit) {
+        __builtin_amdgcn_s_sleep(2);
+        x = __hip_atomic_load(w + (size_t)r * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ++spin;
+      }
+      if ((uint32_t)(x >> 32) != gen) {
+        ++timeouts;
+        continue;
+      }
+      a = fminf(a, __uint_as_float((uint32_t)x << 16));
+      b = fmaxf(b, __uint_as_float((uint32_t)x & 0xFFFF0000u));
+    }
+  }
+}
+
+// FORM: the row slots (kPartRegSlots, kPartLdsSlots).
 // WIDE (more than kSerialPartners partners): every thread of the workgroup
 // polls partners; else one thread per channel polls them all (its own
 // instantiation, so the common case keeps the smaller register footprint).
@@ -503,8 +543,14 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       const int chx = tid % D;
       float a = __builtin_inff(), b = -__builtin_inff();
       uint32_t timeouts = 0;
-      for (uint32_t r = (uint32_t)tid / D; r < parts; r += kPartThreads / D)
-        if (r != q) fold_partner(buf + (size_t)r * D + chx, gen, a, b, timeouts);
+      // (the longest form one word at a time: four in flight spill there, 52
+      // bytes a lane instead of 12)
+      if constexpr (FORM == 0) {
+        for (uint32_t r = (uint32_t)tid / D; r < parts; r += kPartThreads / D)
+          if (r != q) fold_partner(buf + (size_t)r * D + chx, gen, a, b, timeouts);
+      } else {
+        fold_partners<4>(buf + chx, D, (uint32_t)tid / D, kPartThreads / D, parts, q, gen, a, b, timeouts);
+      }
       if (timeouts) __hip_atomic_fetch_add(ex, (uint64_t)timeouts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (a <= b) {
         atomicMin(&red[chx], a);
@@ -522,8 +568,12 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         __hip_atomic_store(buf + (size_t)q * D + tid, tagged_range(a, b, gen), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
         uint32_t timeouts = 0;
-        for (uint32_t r = 0; r < parts; ++r)
-          if (r != q) fold_partner(buf + (size_t)r * D + tid, gen, a, b, timeouts);
+        if constexpr (FORM == 0) {
+          for (uint32_t r = 0; r < parts; ++r)
+            if (r != q) fold_partner(buf + (size_t)r * D + tid, gen, a, b, timeouts);
+        } else {
+          fold_partners<kSerialPartners>(buf + tid, D, 0, 1, parts, q, gen, a, b, timeouts);
+        }
         if (timeouts) __hip_atomic_fetch_add(ex, (uint64_t)timeouts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       const GroupScale gs = group_scale<LEVELS>(a, b);
@@ -730,14 +780,14 @@ __global__ void zero_words_kernel(uint64_t* w, uint32_t n) {
 
 int kivi_part_capacity(int D, int form = 0) { return part_slots(form) * kPartWaves * (512 / D); }
 
-// Fewest workgroups per slice of the resident kernel, 0 for the split kernels.  A
-// grid holds 8 groups per 8 P workgroups, so past 8 partners P is rounded up
-// to 16 or 32, which fill every compute unit; each partner keeps at least one
-// row ((P - 1) ceil(T / P) < T holds for T > (P - 1)^2).
+// Fewest workgroups that hold a slice, 0 if more than kMaxPartners are needed
+// (split kernels).  A grid holds 8 groups per 8 P workgroups, so past 8
+// partners P is rounded up to 16 or 32, which fill every compute unit; each
+// partner keeps at least one row ((P - 1) ceil(T / P) < T holds for T > (P - 1)^2).
 int kivi_partners(int T, int D) {
   const int cap = kivi_part_capacity(D);
   int parts = (T + cap - 1) / cap;
-  if (parts > kMaxPartners || (uint64_t)T * D * 2 >= (1ull << 31)) return 0;  // split kernels
+  if (parts > kMaxPartners || (uint64_t)T * D * 2 >= (1ull << 31)) return 0;
   if (parts > kSerialPartners) parts = parts <= 16 ? 16 : 32;
   if ((uint64_t)(parts - 1) * (uint64_t)((T + parts - 1) / parts) >= (uint64_t)T) return 0;
   return parts;
@@ -788,48 +838,54 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   int cus = 0;
   hipError_t e = grid_cus(&cus);
   if (e != hipSuccess) return e;
-  const int fewest = kivi_partners(p.T, D);
-  if (fewest > 0 && (fewest == 1 || has_ws)) {
-    // Workgroups per slice and form, by the time of the call in twentieths of
-    // a full slot: a round (one slice per group) takes its used slots, a third
-    // of the empty ones (they load the last row again) and the exchange, three.
-    // Measured (2-bit keys at head_dim 128, T = 3000, whole calls, one box):
-    // 28 slices in place, 2 workgroups of the longest form 30.1 us, 8 of it
-    // 30.3, 6 of the shortest 21.6; 56 slices, 2 of the longest 35.0, 4 of the
-    // middle one 31.2, 6 of the shortest (two rounds) 34.3; 280 slices, 2 of
-    // the longest 111.6, 4 of the middle one 113.2, 6 of the shortest 115.5;
-    // 3584 slices (3 bits) 1346, 1400 and 1501.  Shorter forms are therefore
-    // taken for one round, or when they hold the slice in the fewest
-    // workgroups.
-    uint64_t best = ~0ull;
-    for (int form = 0; form < kPartForms; ++form) {
-      for (int parts = fewest; parts <= (has_ws ? kMaxPartners : 1); parts += parts < kSerialPartners ? 1 : parts) {
-        // groups held at once, one workgroup per compute unit (its registers
-        // and, in the longest form, its LDS admit one)
-        uint32_t cap = (uint32_t)cus / (uint32_t)parts;
-        if (parts > 1) cap = std::min(cap, (uint32_t)(kExMaxWgs / parts));
-        cap = cap / 8u * 8u;
-        const uint32_t rows = (uint32_t)((p.T + parts - 1) / parts);
-        if (cap == 0 || rows > (uint32_t)kivi_part_capacity(D, form)) continue;  // every row fits a slot
-        if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;             // every partner has a row
-        const uint32_t groups = std::min((pl->n_items + 7u) / 8u * 8u, cap);
-        const uint32_t rounds = (pl->n_items + groups - 1) / groups;
-        if (form > 0 && rounds > 1 && parts > fewest) continue;
-        const uint32_t per_slot = (uint32_t)(kPartWaves * (512 / D));
-        const uint32_t used = (rows + per_slot - 1) / per_slot;
-        const uint64_t cost = (uint64_t)rounds * (20u * used + 7u * ((uint32_t)part_slots(form) - used) + 60u);
-        if (cost >= best) continue;
-        best = cost;
-        pl->resident = true;
-        pl->form = form;
-        pl->parts = parts;
-        pl->groups = groups;
-        pl->rows_per_part = rows;
-        pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * 2 * parts * D) : 0;
-      }
+  // The resident kernel's workgroups per slice and form, by the time of the
+  // call in twentieths of a slot's time with every compute unit loading: a
+  // round (one slice per group) takes its rows at the chip's rate, or a
+  // workgroup's own at 20/11 of its share if that is longer, a third of the
+  // empty slots (they load the last row again) and the exchange, three slots.
+  // Measured (2-bit keys at head_dim 128, T = 3000, whole
+  // calls): 28 slices in place, 2 workgroups of the longest form 30.1 us, 8 of
+  // it 30.3, 8 of the shortest 22.0; 56 slices, 2 of the longest 35.0, 4 of the
+  // middle one 31.2, 6 of the shortest (two rounds) 34.3; 280 slices, 2 of the
+  // longest 111.6, 4 of the middle one 113.2, 6 of the shortest 115.5; 3584
+  // slices (3 bits) 1346, 1400 and 1501.  So more workgroups of a shorter form
+  // than hold the slice are taken for one round only.
+  // Past kSerialPartners only as many as hold the slice: the dispatcher deals
+  // workgroups to the 8 XCDs in turn, so a group's partners follow each other
+  // on one XCD, and of up to four kernels on separate queues that share its 32
+  // compute units one has 8 or more workgroups there, a whole group, which
+  // then needs no other to finish.
+  const uint32_t wgs = (uint32_t)std::min(cus, kExMaxWgs);  // one workgroup per compute unit
+  const uint32_t fewest = (uint32_t)kivi_partners(p.T, D);
+  const uint32_t most = has_ws ? std::max(fewest, (uint32_t)kSerialPartners) : 1u;
+  uint64_t best = ~0ull;
+  for (int form = 0; form < kPartForms && fewest > 0; ++form) {
+    for (uint32_t parts = fewest; parts <= most; ++parts) {
+      const uint32_t cap = wgs / parts / 8u * 8u;  // groups held at once
+      const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
+      if (cap == 0 || rows > (uint32_t)kivi_part_capacity(D, form)) continue;  // every row fits a slot
+      if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;             // every partner has a row
+      const uint32_t groups = std::min((pl->n_items + 7u) / 8u * 8u, cap);
+      const uint32_t rounds = (pl->n_items + groups - 1) / groups;
+      if (form > 0 && rounds > 1 && parts > fewest) continue;
+      const uint32_t per_slot = (uint32_t)(kPartWaves * (512 / D));
+      const uint32_t used = (rows + per_slot - 1) / per_slot;
+      const uint32_t fixed = 7u * ((uint32_t)part_slots(form) - used) + 60u;
+      auto round_cost = [&](uint64_t active) {  // groups with a slice in this round
+        return std::max<uint64_t>(11u * used, 20u * active * (uint64_t)p.T / ((uint64_t)per_slot * wgs)) + fixed;
+      };
+      const uint64_t cost = (rounds - 1) * round_cost(groups) + round_cost(pl->n_items - (rounds - 1) * groups);
+      if (cost >= best) continue;
+      best = cost;
+      pl->resident = true;
+      pl->form = form;
+      pl->parts = (int)parts;
+      pl->groups = groups;
+      pl->rows_per_part = rows;
+      pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * 2 * parts * D) : 0;
     }
-    if (pl->resident) return hipSuccess;
   }
+  if (pl->resident) return hipSuccess;
   if (has_ws) {
     pl->split = true;
     pl->clear_words = (uint32_t)(kExHeader + (uint64_t)std::min(pl->n_items, kSplitBatch) * D);

@@ -187,7 +187,7 @@ def _form_cases():
     out = []
     for D in (64, 128, 256):
         r = 8192 // D
-        for cus, P, slots in (("256", 6, 8), ("256", 4, 15), ("256", 32, 8), ("64", 8, 24), ("48", 2, 24)):
+        for cus, P, slots in (("256", 6, 8), ("256", 4, 15), ("256", 32, 15), ("64", 8, 24), ("48", 2, 24)):
             out += [(D, cus, P * slots * r + d) for d in (-3, 0, 1) if P * slots * r + d > 24 * r]
     return out
 
