@@ -301,8 +301,8 @@ static hipError_t launch_f_dim(const Params& p, int D, int bits, Tensors which, 
   }
 }
 
-// Value tiles of the KIVI-style and AKVQ-style bases run as a launch of the
-// min-max instantiation, which needs fewer registers than their key paths
+// Past kOneLaunchBytesFake the value tiles of the KIVI-style and AKVQ-style
+// bases run as a launch of the min-max instantiation, which needs fewer registers than their key paths
 // (as in launch_quantize); with KIVI keys over the whole sequence the whole
 // launch does, its key blocks listing the protected key slices alone (out of
 // place they are copied; in place they need nothing, and the launch takes the
@@ -315,9 +315,11 @@ hipError_t launch_fake_quantize(const Params& p, int base, int D, int bits, bool
   }
   if (base == HG_BASE_MINMAX) return launch_f_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kBoth, norms, stream);
   if (base != HG_BASE_KIVI && base != HG_BASE_AKVQ) return hipErrorInvalidValue;
-  hipError_t e = base == HG_BASE_KIVI ? launch_f_dim<HG_BASE_KIVI>(p, D, bits, Tensors::kKeys, norms, stream)
-                                      : launch_f_dim<HG_BASE_AKVQ>(p, D, bits, Tensors::kKeys, norms, stream);
-  if (e != hipSuccess) return e;
+  const bool one = image_bytes(p, D) < kOneLaunchBytesFake;
+  const Tensors which = one ? Tensors::kBoth : Tensors::kKeys;
+  const hipError_t e = base == HG_BASE_KIVI ? launch_f_dim<HG_BASE_KIVI>(p, D, bits, which, norms, stream)
+                                            : launch_f_dim<HG_BASE_AKVQ>(p, D, bits, which, norms, stream);
+  if (one || e != hipSuccess) return e;
   return launch_f_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kValues, false, stream);
 }
 

@@ -94,6 +94,27 @@ struct Params {
 // decode_launch_block), then every value slice.
 enum class Tensors { kBoth, kKeys, kValues, kKeptKeysAndValues };
 
+// Calls of the KIVI-style and AKVQ-style bases whose image rows of K and V are
+// together below these bytes run as one launch of the base's instantiation,
+// larger ones as a launch of the keys and a min-max launch of the values (whose
+// registers, tiles and occupancy cap are then those of the min-max path).  One
+// launch saves a launch and the drain of the first one; the separate
+// instantiation pays once the values' streaming outweighs that.  Measured, two
+// launches -> one (us, device time, 2 bits, head_dim 128):
+//            MB      2.7            48            386           772          3087
+//  KIVI quantize  8.6 -> 5.4  16.7 -> 12.5  81.0 -> 74.7   162 -> 155   647 -> 651
+//  dequantize     5.9 -> 3.5  11.4 ->  9.8  72.7 -> 70.2   140 -> 138   641 -> 677
+//  one-pass       7.7 -> 4.9  18.7 -> 17.3   122 ->  117   255 -> 256  1068 -> 1079
+//            MB      14             56            445           889          1778
+//  AKVQ quantize  8.4 -> 5.4  19.2 -> 15.2   101 ->  95    190 -> 184   376 -> 372
+//  dequantize     8.4 -> 5.6  15.6 -> 12.0    87 ->  81    165 -> 162   381 -> 383
+//  one-pass      10.5 -> 6.9  25.3 -> 21.3   153 -> 149    300 -> 299   613 -> 618
+constexpr uint64_t kOneLaunchBytes = 1ull << 30;
+constexpr uint64_t kOneLaunchBytesFake = 1ull << 29;
+inline uint64_t image_bytes(const Params& p, int D) {
+  return 2ull * (uint64_t)p.L * p.B * p.H * (uint64_t)p.n * D * 2;
+}
+
 // Dispatch over (base, D, bits); return hipSuccess or the launch error.
 // With `norms`, the quantize kernel also writes the squared key norms (AKVQ).
 hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norms, hipStream_t stream);

@@ -345,8 +345,8 @@ static hipError_t launch_q_dim(const Params& p, int D, int bits, Tensors which, 
 }
 
 // The KIVI-style and AKVQ-style bases quantize values exactly as min-max
-// does (per token, unrotated), so their value tiles run as a launch of the
-// min-max instantiation: a kernel holds the registers of its largest path,
+// does (per token, unrotated), so past kOneLaunchBytes their value tiles run
+// as a launch of the min-max instantiation: a kernel holds the registers of its largest path,
 // and the key paths (KIVI groups, rotation) need more than the per-token
 // path, which would leave the value tiles with fewer waves per SIMD.  With
 // KIVI keys over the whole sequence this launch only copies protected keys
@@ -359,9 +359,11 @@ hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norm
     return launch_q_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kKeptKeysAndValues, norms, stream);
   if (base == HG_BASE_MINMAX) return launch_q_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kBoth, norms, stream);
   if (base != HG_BASE_KIVI && base != HG_BASE_AKVQ) return hipErrorInvalidValue;
-  hipError_t e = base == HG_BASE_KIVI ? launch_q_dim<HG_BASE_KIVI>(p, D, bits, Tensors::kKeys, norms, stream)
-                                      : launch_q_dim<HG_BASE_AKVQ>(p, D, bits, Tensors::kKeys, norms, stream);
-  if (e != hipSuccess) return e;
+  const bool one = image_bytes(p, D) < kOneLaunchBytes;
+  const Tensors which = one ? Tensors::kBoth : Tensors::kKeys;
+  const hipError_t e = base == HG_BASE_KIVI ? launch_q_dim<HG_BASE_KIVI>(p, D, bits, which, norms, stream)
+                                            : launch_q_dim<HG_BASE_AKVQ>(p, D, bits, which, norms, stream);
+  if (one || e != hipSuccess) return e;
   return launch_q_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kValues, false, stream);
 }
 

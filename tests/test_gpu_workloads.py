@@ -57,3 +57,20 @@ def test_tensors_past_4_gib(kivi_group):
 
 def test_one_pass_past_4_gib():
     wholecache.assert_whole(wholecache.fake_quantize(PAST_4GIB, inplace=False), PAST_4GIB)
+
+
+# The KIVI-style and AKVQ-style bases run as one launch below 1 GiB of image
+# rows of K and V (one-pass 512 MiB) and as a launch each above: caches just
+# below and just above, at the head dims and widths that the workloads of that
+# size do not have.
+@pytest.mark.parametrize("base,D,bits,H", [("kivi", 64, 3, 8), ("akvq", 256, 4, 2)])
+@pytest.mark.parametrize("past", [False, True])
+def test_one_launch_limit(base, D, bits, H, past):
+    n = (1 << 30) // (4 * 8 * 4 * H * D) + (1 if past else -1)
+    w = synthkv.Workload(f"limit-{base}-{past}", L=8, B=4, H=H, T=n + 5, D=D, img_start=3, img_len=n, bits=bits,
+                         base=base, keys_only=0, n_protected=5, k_outliers=4, k_outlier_scale=10.0, kivi_group=32,
+                         seed=5)
+    assert (4 * w.L * w.B * w.H * n * D >= 1 << 30) == past
+    wholecache.assert_whole(wholecache.quantize_dequantize(w), w)
+    half = w.with_(B=2, name=w.name + "-one-pass")
+    wholecache.assert_whole(wholecache.fake_quantize(half, inplace=past), half)
