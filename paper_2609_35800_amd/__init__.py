@@ -102,22 +102,26 @@ def _check(status: int) -> None:
         raise HeadGuardError(status, hg_last_error())
 
 
-def _mask_arg(mask) -> np.ndarray:
-    m = np.ascontiguousarray(np.asarray(mask, dtype=np.uint8).reshape(-1))
-    return m
+# Marshalling is what bounds the calls of one layer (its kernels run 4-8 us):
+# the mask goes as the address of a bytes copy (0.3 us; ctypes views of the
+# array 2.7), the descriptor's fields by position, and the stream as the raw
+# handle torch keeps (a Stream object costs four times as much).  Calls of one
+# layer: quantize 10.8 -> 6.8 us (4 heads, 1360 tokens), dequantize 14.4 -> 10.4
+# (8 heads, 3456 tokens, rotated keys, retention).
+
+def _mask_arg(mask) -> bytes:
+    return np.asarray(mask, dtype=np.uint8).tobytes()
 
 
 def _ptr(t) -> Optional[int]:
-    if t is None:
-        return None
-    if isinstance(t, int):
+    if t is None or isinstance(t, int):
         return t
-    return t.data_ptr() if t.numel() > 0 else None
+    return t.data_ptr()  # 0 for a tensor without elements
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -135,12 +139,12 @@ def make_config(L, B, H, T, D, img_start, img_len, bits, base, keys_only, kivi_g
 def hg_packed_sizes(cfg: hg_config, protect_mask) -> Dict[str, int]:
     m = _mask_arg(protect_mask)
     out = hg_sizes()
-    _check(_lib.hg_packed_sizes(C.byref(cfg), m.ctypes.data_as(C.c_void_p), C.byref(out)))
+    _check(_lib.hg_packed_sizes(C.byref(cfg), m, C.byref(out)))
     return {n: getattr(out, n) for n, _ in hg_sizes._fields_}
 
 
 def _packed_struct(packed: Dict[str, torch.Tensor]) -> hg_packed:
-    return hg_packed(**{n: _ptr(packed.get(n)) for n in PACKED})
+    return hg_packed(*map(_ptr, map(packed.get, PACKED)))
 
 
 def hg_quantize(cfg: hg_config, K: torch.Tensor, V: torch.Tensor, protect_mask,
@@ -148,7 +152,7 @@ def hg_quantize(cfg: hg_config, K: torch.Tensor, V: torch.Tensor, protect_mask,
     """Enqueue quantize+pack of the image KV of K, V into `packed` buffers."""
     m = _mask_arg(protect_mask)
     pk = _packed_struct(packed)
-    _check(_lib.hg_quantize(C.byref(cfg), _ptr(K), _ptr(V), m.ctypes.data_as(C.c_void_p),
+    _check(_lib.hg_quantize(C.byref(cfg), _ptr(K), _ptr(V), m,
                             C.byref(pk), _stream(stream)))
 
 
@@ -157,7 +161,7 @@ def hg_dequantize(cfg: hg_config, protect_mask, packed: Dict[str, torch.Tensor],
     """Enqueue reconstruction of the image rows of K_out, V_out."""
     m = _mask_arg(protect_mask)
     pk = _packed_struct(packed)
-    _check(_lib.hg_dequantize(C.byref(cfg), m.ctypes.data_as(C.c_void_p), C.byref(pk),
+    _check(_lib.hg_dequantize(C.byref(cfg), m, C.byref(pk),
                               _ptr(K_out), _ptr(V_out), _stream(stream)))
 
 
@@ -172,7 +176,7 @@ def hg_fake_quantize(cfg: hg_config, K: torch.Tensor, V: torch.Tensor, protect_m
     m = _mask_arg(protect_mask)
     ws = _ptr(workspace)
     nbytes = workspace.numel() * workspace.element_size() if ws is not None else 0
-    _check(_lib.hg_fake_quantize(C.byref(cfg), _ptr(K), _ptr(V), m.ctypes.data_as(C.c_void_p),
+    _check(_lib.hg_fake_quantize(C.byref(cfg), _ptr(K), _ptr(V), m,
                                  _ptr(K_out), _ptr(V_out), ws, nbytes, _stream(stream)))
 
 
@@ -183,7 +187,7 @@ def hg_fake_quantize_noalloc(cfg: hg_config, K: torch.Tensor, V: torch.Tensor, p
     array (HG_NOALLOC_SCRATCH_BYTES per GPU): nothing is allocated;
     overlapping calls on one GPU race on that array."""
     m = _mask_arg(protect_mask)
-    _check(_lib.hg_fake_quantize_noalloc(C.byref(cfg), _ptr(K), _ptr(V), m.ctypes.data_as(C.c_void_p),
+    _check(_lib.hg_fake_quantize_noalloc(C.byref(cfg), _ptr(K), _ptr(V), m,
                                          _ptr(K_out), _ptr(V_out), _stream(stream)))
 
 
