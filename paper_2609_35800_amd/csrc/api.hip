@@ -354,7 +354,7 @@ static int run(bool quantize, const hg_config* cfg, const uint16_t* K, const uin
     e = step([&] { return hg::launch_kivi_seq(p, cfg->D, cfg->bits, false, kivi_ws, true, stream); });
   if (e == hipSuccess && p.k > 0 && quantize)
     e = step([&] { return hg::launch_retain_select(p, cfg->D, hg::RowCopy::kGather, stream); });
-  if (e == hipSuccess && p.k > 0 && !quantize)
+  if (e == hipSuccess && p.k > 0 && !quantize && !hg::retain_in_dequantize(p, cfg->D))
     e = step([&] { return hg::launch_retain_rows(p, cfg->D, hg::RowCopy::kScatter, stream); });
   if (e != hipSuccess) return fail(HG_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
   return ok();

@@ -25,15 +25,42 @@ namespace hg {
 template <int BASE, int D>
 constexpr int kDequantTokens = (D == 128 && BASE != HG_BASE_AKVQ) ? 16 : kWaveTokens;
 
+// Token retention: lane j < TOKENS of the result holds 1 + the list position of
+// token t_first + j, or 0 where that token is not in the list.  The lanes read
+// the list 64 entries at a time and push the positions of the tile's entries
+// to the tokens' lanes (the rest go to lane 63, whose value is then cleared);
+// entries outside the span are left out, and the order of the list is free.
+template <int TOKENS>
+__device__ __forceinline__ int retained_places(const uint32_t (&list)[kFusedRetained / 64], int k, int t_first, int n,
+                                               int lane) {
+  static_assert(TOKENS <= 32, "a 32-bit mask; lane 63 takes what is not in the tile");
+  int place = 0;
+  const int count = min(TOKENS, n - t_first);
+#pragma unroll
+  for (int w = 0; w < kFusedRetained / 64; ++w) {
+    if (64 * w >= k) break;
+    const int i = 64 * w + lane;
+    const uint32_t t = list[w] - (uint32_t)t_first;
+    const bool in = i < k && t < (uint32_t)count;
+    if (__ballot(in) == 0) continue;
+    const int got = __builtin_amdgcn_ds_permute(in ? 4 * (int)t : 4 * 63, in ? i + 1 : 0);
+    place = lane < TOKENS && got > 0 ? got : place;
+  }
+  return place;
+}
+
 // Per-token groups.  A token row is held by D/8 lanes, lane c holding
 // channels [8c, 8c + 8), so each 16-byte store instruction of the wavefront
 // writes 64/(D/8) whole consecutive token rows (one contiguous 1 KiB run for
 // D = 128; two 512-byte rows at 256).  AKVQ keys are rotated back across the
 // row's lanes first.
-template <int D, int BITS, bool ROTATE, int TOKENS>
+// RET: the slice's retained tokens (`idx`, k <= kFusedRetained of them) that
+// fall in this tile are stored from their BF16 rows `ret` instead.
+template <int D, int BITS, bool ROTATE, int TOKENS, bool RET>
 __device__ __forceinline__ void dequantize_tokens(const uint8_t* __restrict__ codes,
                                                   const uint32_t* __restrict__ meta,
-                                                  uint16_t* __restrict__ rows,
+                                                  uint16_t* __restrict__ rows, const int32_t* __restrict__ idx,
+                                                  const uint16_t* __restrict__ ret, int k,
                                                   int t_first, int n, int lane) {
   constexpr int LPT = D / 8;               // lanes per token row
   constexpr int TPI = 64 / LPT;            // token rows per instruction
@@ -43,27 +70,53 @@ __device__ __forceinline__ void dequantize_tokens(const uint8_t* __restrict__ co
   const int c = lane % LPT;
   const int r = lane / LPT;
 
+  uint32_t list[kFusedRetained / 64] = {};  // the list, 64 entries at a time
+  if constexpr (RET) {
+#pragma unroll
+    for (int w = 0; w < kFusedRetained / 64; ++w)
+      if (64 * w < k) list[w] = (uint32_t)idx[min(64 * w + lane, k - 1)];
+  }
   // Past-the-end tokens read the last token (not stored): loads unconditional.
   uint32_t pc[NP], mw[NP];
 #pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    const int t = min(t_first + r + TPI * k, n - 1);
-    pc[k] = load_piece8<BITS, ROW>(codes + (size_t)t * ROW, c);
-    mw[k] = meta[t];
+  for (int i = 0; i < NP; ++i) {
+    const int t = min(t_first + r + TPI * i, n - 1);
+    pc[i] = load_piece8<BITS, ROW>(codes + (size_t)t * ROW, c);
+    mw[i] = meta[t];
   }
+  const int place = RET ? retained_places<TOKENS>(list, k, t_first, n, lane) : 0;
+  const uint32_t own = RET ? (uint32_t)__ballot(place > 0) : 0u;  // tokens whose BF16 rows are stored below
 #pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    const int t = t_first + r + TPI * k;
-    const float S = bf16_as_float(mw[k] & 0xFFFFu);
-    const float m = bf16_as_float(mw[k] >> 16);
+  for (int i = 0; i < NP; ++i) {
+    const int t = t_first + r + TPI * i;
+    const float S = bf16_as_float(mw[i] & 0xFFFFu);
+    const float m = bf16_as_float(mw[i] >> 16);
     float y[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf((float)((pc[k] >> (BITS * e)) & kMask), S, m);
+    for (int e = 0; e < 8; ++e) y[e] = __builtin_fmaf((float)((pc[i] >> (BITS * e)) & kMask), S, m);
     if constexpr (ROTATE) fwht_row<D>(y, c);
-    if (t < n) {
+    if (t < n && !((own >> (r + TPI * i)) & 1u)) {
       u32x4 v = {pack_bf16x2_hw(y[0], y[1]), pack_bf16x2_hw(y[2], y[3]), pack_bf16x2_hw(y[4], y[5]),
                  pack_bf16x2_hw(y[6], y[7])};
       store_nt((u32x4*)(rows + (size_t)t * D + 8 * c), v);
+    }
+  }
+  if constexpr (RET) {
+    if (own == 0) return;
+    constexpr int U = NP < 4 ? NP : 4;  // rows in flight per lane (all of them cost the rotated keys 30 registers)
+#pragma unroll 1
+    for (int i0 = 0; i0 < NP; i0 += U) {
+      u32x4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // (tokens that are not retained re-read the list's first row)
+        const int at = max(__shfl(place, r + TPI * (i0 + u)) - 1, 0);
+        v[u] = *(const u32x4*)(ret + (size_t)at * D + 8 * c);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = r + TPI * (i0 + u);
+        if ((own >> j) & 1u) store_nt((u32x4*)(rows + (size_t)(t_first + j) * D + 8 * c), v[u]);
+      }
     }
   }
 }
@@ -116,7 +169,8 @@ __device__ __forceinline__ void dequantize_kivi_keys(const uint8_t* __restrict__
   }
 }
 
-template <int BASE, int D, int BITS>
+// RET: token retention, its rows written by this kernel (see kFusedRetained).
+template <int BASE, int D, int BITS, bool RET>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves))) void dequantize_kernel(const Params p) {
   const Slice sl = decode_block(p, blockIdx.x);
   const int lane = threadIdx.x & 63;
@@ -138,10 +192,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
     dequantize_kivi_keys<D, BITS, kTokens>(codes, p.meta[0] + slab * p.ngroups * D, rows, t_first, group, p.n, lane);
   } else {
     const uint32_t* meta = p.meta[sl.X] + slab * p.n;
+    const int32_t* idx = RET ? p.ret_idx + (size_t)sl.s * p.k : nullptr;
+    const uint16_t* ret = RET ? p.ret[sl.X] + slab * p.k * D : nullptr;
     if (BASE == HG_BASE_AKVQ && sl.X == 0)
-      dequantize_tokens<D, BITS, true, kTokens>(codes, meta, rows, t_first, p.n, lane);
+      dequantize_tokens<D, BITS, true, kTokens, RET>(codes, meta, rows, idx, ret, p.k, t_first, p.n, lane);
     else
-      dequantize_tokens<D, BITS, false, kTokens>(codes, meta, rows, t_first, p.n, lane);
+      dequantize_tokens<D, BITS, false, kTokens, RET>(codes, meta, rows, idx, ret, p.k, t_first, p.n, lane);
   }
 }
 
@@ -165,7 +221,14 @@ static hipError_t launch_d(const Params& p, Tensors which, hipStream_t stream) {
   const uint64_t row_bytes = blocks / (uint64_t)pd.tiles * (uint64_t)p.n * D * 2;  // rows the launch writes
   const int waves =
       BASE == HG_BASE_MINMAX && row_bytes >= kDequantizeSmallBytes ? kDequantizeWavesMinMax : kDequantizeWaves;
-  hipLaunchKernelGGL((dequantize_kernel<BASE, D, BITS>), dim3((uint32_t)blocks), dim3(kThreads),
+  if constexpr (BASE == HG_BASE_AKVQ) {
+    if (retain_in_dequantize(p, D)) {  // keys and values in this launch
+      hipLaunchKernelGGL((dequantize_kernel<BASE, D, BITS, true>), dim3((uint32_t)blocks), dim3(kThreads),
+                         occupancy_lds(waves), stream, pd);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((dequantize_kernel<BASE, D, BITS, false>), dim3((uint32_t)blocks), dim3(kThreads),
                      occupancy_lds(waves), stream, pd);
   return hipGetLastError();
 }

@@ -145,6 +145,19 @@ hipError_t launch_key_norms(const Params& p, int D, hipStream_t stream);
 enum class RowCopy { kGather, kScatter, kCacheToOut };
 hipError_t launch_retain_select(const Params& p, int D, RowCopy mode, hipStream_t stream);
 hipError_t launch_retain_rows(const Params& p, int D, RowCopy mode, hipStream_t stream);
+// Calls of one dequantize launch with at most kFusedRetained retained tokens per
+// (l, b, h) store their rows in that kernel, each wavefront those of its tile.
+// Longer lists, which every wavefront would have to read (4 loads of 64 entries
+// at the limit), and calls of two launches are written back by
+// launch_retain_rows.  Write-back launch -> in the kernel (us, 8 heads, 3456
+// tokens, 67 retained, 2 bits; 4 bits): one layer 9.7 -> 7.4 (9.7 -> 7.1), 4
+// prompts 16.1 -> 13.5 (16.6 -> 13.2), 16 prompts 47.1 -> 43.5 (49.3 -> 46.1), 64
+// prompts 170 -> 168 (213 -> 208); 256 prompts, two launches, 776 -> 857 (825 ->
+// 845), their wavefronts waiting for the list, 773 (809) without occupancy caps.
+constexpr int kFusedRetained = 256;
+inline bool retain_in_dequantize(const Params& p, int D) {
+  return p.k > 0 && p.k <= kFusedRetained && image_bytes(p, D) < kOneLaunchBytes;
+}
 
 // Host side: the one-pass call (api.hip) with its token-retention workspace
 // supplied by `get_ws(need, &ws)` after the host-side argument checks, only

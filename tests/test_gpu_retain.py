@@ -58,6 +58,54 @@ def test_long_spans(img_len):
     _assert_exact(compare_full(w, K, V, np.zeros(w.L * w.H, np.uint8)), w.name)
 
 
+# Lists at the lengths where dequantize stores the retained rows in its own
+# kernel (64 entries a load, up to 256) or in a launch of its own.
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("img_len,permille", [(640, 100), (650, 100), (1280, 200), (1285, 200), (255, 1000)])
+def test_route_boundaries(D, img_len, permille):
+    for bits in (2, 4):
+        w = retain_case(D=D, bits=bits, img_len=img_len, img_start=5, text=3, L=1, B=1, H=3, n_protected=1,
+                        permille=permille)
+        K, V = synthkv.gen_kv(w)
+        _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), w.name)
+
+
+def test_list_in_any_order():
+    """Dequantize writes back the rows that the list names, whatever its order,
+    and leaves out entries outside the span (both list lengths)."""
+    import paper_2609_35800_amd as hg
+    for permille in (100, 500):
+        w = retain_case(img_len=700, permille=permille, n_protected=0)
+        K, V = synthkv.gen_kv(w)
+        cfg, mask = hg.make_config(**w.config_fields()), synthkv.protect_mask(w)
+        packed = hg.alloc_packed(cfg, mask)
+        hg.hg_quantize(cfg, K.cuda(), V.cuda(), mask, packed)
+        k = hg.hg_packed_sizes(cfg, mask)["retain_count"]
+        out = [torch.zeros(K.shape, dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+        hg.hg_dequantize(cfg, mask, packed, out[0], out[1])
+        idx = packed["ret_idx"].view(torch.int32).view(-1, k)
+        perm = torch.randperm(k, generator=torch.Generator().manual_seed(k)).cuda()
+        idx.copy_(idx[:, perm].clone())
+        for n in ("ret_k", "ret_v"):
+            rows = packed[n].view(torch.int16).view(-1, k, w.D)
+            rows.copy_(rows[:, perm].clone())
+        hg.hg_dequantize(cfg, mask, packed, out[2], out[3])
+        assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+        idx[:, ::2] = torch.tensor([-1, w.img_len, 1 << 30, -(1 << 31)], dtype=torch.int32,
+                                   device="cuda").repeat(k)[: idx[:, ::2].shape[1]]
+        hg.hg_dequantize(cfg, mask, packed, out[2], out[3])
+        lo, hi = w.img_start, w.img_start + w.img_len
+        kept = torch.zeros(out[0].shape[:4], dtype=torch.bool, device="cuda").view(-1, w.T)
+        kept[:, lo:hi].scatter_(1, idx[:, 1::2].long(), True)
+        raw = {n: (t.clone() if n == "ret_idx" else t) for n, t in packed.items()}
+        raw["ret_idx"].fill_(0xFF)  # every entry -1: the reconstruction alone
+        hg.hg_dequantize(cfg, mask, raw, out[0], out[1])
+        for got, plain, src in ((out[2], out[0], K.cuda()), (out[3], out[1], V.cuda())):
+            want = torch.where(kept.view(*got.shape[:4], 1), src, plain)
+            want[..., :lo, :], want[..., hi:, :] = 0, 0
+            assert torch.equal(got, want)
+
+
 def _integer_kv(w, lo, hi, seed):
     g = torch.Generator().manual_seed(seed)
     shape = (w.L, w.B, w.H, w.T, w.D)
