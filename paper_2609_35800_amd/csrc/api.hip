@@ -344,15 +344,18 @@ static int run(bool quantize, const hg_config* cfg, const uint16_t* K, const uin
     if (pe != hipSuccess) return fail(HG_ERR_HIP, "KIVI key kernel plan failed: %s", hipGetErrorString(pe));
     p.clear = (uint64_t*)kivi_ws;
   }
+  const bool select_now = quantize && hg::select_with_values(p, cfg->D, cfg->bits);
   LaunchSteps step;
   hipError_t e = step([&] {
-    return quantize ? hg::launch_quantize(p, cfg->base, cfg->D, cfg->bits, retain, stream)
+    return quantize ? hg::launch_quantize(p, cfg->base, cfg->D, cfg->bits, retain, select_now, stream)
                     : hg::launch_dequantize(p, cfg->base, cfg->D, cfg->bits, stream);
   });
   p.clear_words = 0;
   if (e == hipSuccess && quantize && p.kivi_whole)
     e = step([&] { return hg::launch_kivi_seq(p, cfg->D, cfg->bits, false, kivi_ws, true, stream); });
-  if (e == hipSuccess && p.k > 0 && quantize)
+  if (e == hipSuccess && select_now)
+    e = step([&] { return hg::launch_quantize_values_select(p, cfg->D, cfg->bits, stream); });
+  else if (e == hipSuccess && p.k > 0 && quantize)
     e = step([&] { return hg::launch_retain_select(p, cfg->D, hg::RowCopy::kGather, stream); });
   if (e == hipSuccess && p.k > 0 && !quantize && !hg::retain_in_dequantize(p, cfg->D))
     e = step([&] { return hg::launch_retain_rows(p, cfg->D, hg::RowCopy::kScatter, stream); });

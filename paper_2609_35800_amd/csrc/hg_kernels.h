@@ -117,7 +117,11 @@ inline uint64_t image_bytes(const Params& p, int D) {
 
 // Dispatch over (base, D, bits); return hipSuccess or the launch error.
 // With `norms`, the quantize kernel also writes the squared key norms (AKVQ).
-hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norms, hipStream_t stream);
+// With `keys_alone` (AKVQ) the values follow with the selection of the retained
+// tokens in launch_quantize_values_select, where select_with_values allows it.
+hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norms, bool keys_alone, hipStream_t stream);
+bool select_with_values(const Params& p, int D, int bits);
+hipError_t launch_quantize_values_select(const Params& p, int D, int bits, hipStream_t stream);
 hipError_t launch_dequantize(const Params& p, int base, int D, int bits, hipStream_t stream);
 hipError_t launch_fake_quantize(const Params& p, int base, int D, int bits, bool norms, hipStream_t stream);
 // KIVI keys over the whole sequence: a persistent grid over the quantized key

@@ -28,6 +28,7 @@
 
 #include "hg_device.h"
 #include "hg_kernels.h"
+#include "hg_retain.h"
 
 namespace hg {
 
@@ -228,10 +229,9 @@ __device__ __forceinline__ void quantize_kivi_keys(const uint16_t* __restrict__ 
 
 // ---------------------------------------------------------------- kernel
 
+// A workgroup's tile of a slice.
 template <int BASE, int D, int BITS, bool NORM>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves))) void quantize_kernel(const Params p) {
-  clear_words_share(p);
-  const Slice sl = decode_launch_block(p, blockIdx.x);
+__device__ __forceinline__ void quantize_tile(const Params& p, const Slice& sl) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int t_first = sl.tile * kBlockTokens + wave * kWaveTokens;
@@ -268,6 +268,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
   }
 }
 
+template <int BASE, int D, int BITS, bool NORM>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves))) void quantize_kernel(const Params p) {
+  clear_words_share(p);
+  quantize_tile<BASE, D, BITS, NORM>(p, decode_launch_block(p, blockIdx.x));
+}
+
+// Token retention: the value tiles and the selection, which needs only the key
+// norms of the launch before.  The first workgroup of each slice's run selects
+// its retained tokens, the others quantize its value tiles, so the selection,
+// a chain of barriers and LDS passes with little traffic, runs among streaming
+// workgroups.  A launch for both and one for the selection -> keys, then values
+// and selection (us, 8 heads, 3456 tokens, 2 bits): one layer 22.9 -> 17.9, 4
+// prompts 34.8 -> 27.2, 64 prompts 218 -> 210, 256 prompts (two launches and one)
+// 811 -> 800; head_dim 256, 64 prompts 434 -> 430.
+template <int D, int BITS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves)))
+void quantize_values_select_kernel(const Params p) {
+  extern __shared__ uint32_t lds_keys[];  // n keys
+  const uint32_t run = (uint32_t)p.tiles + 1u;
+  const uint32_t s = blockIdx.x / run, i = blockIdx.x % run;
+  if (i == 0) {
+    retain_select<true, D, RowCopy::kGather>(p, s, lds_keys);
+    return;
+  }
+  const SliceRoute r = route_slice(p, 1, s);
+  quantize_tile<HG_BASE_MINMAX, D, BITS, false>(p, Slice{1, (int)i - 1, s, r.b, r.kept, r.slot});
+}
+
 // Wavefronts per SIMD of a quantize launch (each measured against 6 on the
 // caches shaped like the workloads):
 //  - 4 for 4-bit codes, whose stores are twice the 2-bit share of the traffic
@@ -294,6 +322,55 @@ constexpr size_t quantize_lds() {
   constexpr int waves = kQuantizeWavesOf<BASE, D, BITS, NORM>;
   static_assert(occupancy_lds(waves) > stage, "the stage fits the reservation");
   return occupancy_lds(waves) - stage;
+}
+
+// Dynamic LDS of the launch of the values with the selection: the values' cap
+// less both parts' static arrays; it holds the norms the selection works on.
+template <int D, int BITS>
+constexpr size_t kValuesSelectLds = quantize_lds<HG_BASE_MINMAX, D, BITS, false>() - kSelectLds;
+
+template <int D>
+static size_t values_select_lds(int bits) {
+  return bits == 2 ? kValuesSelectLds<D, 2> : bits == 3 ? kValuesSelectLds<D, 3> : kValuesSelectLds<D, 4>;
+}
+
+// Spans whose norms fit that LDS (6000 tokens at 2 bits and head_dim 128; 3900
+// at head_dim 256): a larger reservation would cost the value tiles their
+// occupancy, so longer spans select in a launch of their own.
+bool select_with_values(const Params& p, int D, int bits) {
+  const size_t lds = D == 64 ? values_select_lds<64>(bits) : D == 128 ? values_select_lds<128>(bits)
+                                                                      : values_select_lds<256>(bits);
+  const uint64_t blocks = (uint64_t)p.L * p.B * p.H * ((uint64_t)(p.n + kBlockTokens - 1) / kBlockTokens + 1);
+  return p.k > 0 && (size_t)p.n * sizeof(uint32_t) <= lds && blocks <= 0x7FFFFFFFull;
+}
+
+template <int D, int BITS>
+static hipError_t launch_values_select(const Params& p, hipStream_t stream) {
+  Params pq = p;
+  pq.tiles = (p.n + kBlockTokens - 1) / kBlockTokens;
+  const uint32_t blocks = (uint32_t)p.L * p.B * p.H * (uint32_t)(pq.tiles + 1);
+  hipLaunchKernelGGL((quantize_values_select_kernel<D, BITS>), dim3(blocks), dim3(kThreads),
+                     (kValuesSelectLds<D, BITS>), stream, pq);
+  return hipGetLastError();
+}
+
+template <int D>
+static hipError_t launch_values_select_bits(const Params& p, int bits, hipStream_t stream) {
+  switch (bits) {
+    case 2: return launch_values_select<D, 2>(p, stream);
+    case 3: return launch_values_select<D, 3>(p, stream);
+    case 4: return launch_values_select<D, 4>(p, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_quantize_values_select(const Params& p, int D, int bits, hipStream_t stream) {
+  switch (D) {
+    case 64: return launch_values_select_bits<64>(p, bits, stream);
+    case 128: return launch_values_select_bits<128>(p, bits, stream);
+    case 256: return launch_values_select_bits<256>(p, bits, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // The workgroup tiles of a launch: kBlockTokens tokens each.
@@ -354,7 +431,10 @@ static hipError_t launch_q_dim(const Params& p, int D, int bits, Tensors which, 
 // key blocks listing the protected key slices alone (with every key slice
 // listed, the 7/8 that exit at once cost 36 us on the LLaVA-NeXT-shaped
 // cache).
-hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norms, hipStream_t stream) {
+// With token retention the keys are launched alone, whatever the size, and the
+// values with the selection, which needs the keys' norms.
+hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norms, bool keys_alone, hipStream_t stream) {
+  if (keys_alone && base == HG_BASE_AKVQ) return launch_q_dim<HG_BASE_AKVQ>(p, D, bits, Tensors::kKeys, norms, stream);
   if (base == HG_BASE_KIVI && p.kivi_whole)
     return launch_q_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kKeptKeysAndValues, norms, stream);
   if (base == HG_BASE_MINMAX) return launch_q_dim<HG_BASE_MINMAX>(p, D, bits, Tensors::kBoth, norms, stream);

@@ -59,9 +59,11 @@ def test_long_spans(img_len):
 
 
 # Lists at the lengths where dequantize stores the retained rows in its own
-# kernel (64 entries a load, up to 256) or in a launch of its own.
+# kernel (64 entries a load, up to 256) or in a launch of its own, and spans
+# where the selection runs among the value tiles or in a launch of its own.
 @pytest.mark.parametrize("D", [64, 128, 256])
-@pytest.mark.parametrize("img_len,permille", [(640, 100), (650, 100), (1280, 200), (1285, 200), (255, 1000)])
+@pytest.mark.parametrize("img_len,permille", [(640, 100), (650, 100), (1280, 200), (1285, 200), (255, 1000),
+                                              (3900, 20), (4100, 20), (6100, 20), (8300, 20)])
 def test_route_boundaries(D, img_len, permille):
     for bits in (2, 4):
         w = retain_case(D=D, bits=bits, img_len=img_len, img_start=5, text=3, L=1, B=1, H=3, n_protected=1,
