@@ -75,7 +75,9 @@
  * longer than one workgroup holds on chip, several co-resident workgroups
  * (more of them, up to eight, when there are few slices) hold it together and
  * exchange partial ranges through the caller's workspace, waiting for one
- * another (a bounded number of polls); past 32 workgroups' rows, chunks of each slice merge their ranges into the same
+ * another (a bounded number of polls); past 32 workgroups' rows they first
+ * agree that all of them are on the chip, and if not, or past 256 workgroups'
+ * rows, chunks of each slice merge their ranges into the same
  * workspace with atomics and a second launch writes the codes.  The
  * kernel is sized to be resident on an otherwise idle device: a kernel
  * running concurrently on another stream can delay it, and one that keeps

@@ -7,7 +7,7 @@
 // slice, so a slice must be fully read before any of its codes is formed.
 // Three forms:
 //
-// Partitioned resident kernel (T at most 32 workgroups' capacity): a
+// Partitioned resident kernel (T at most 32 workgroups' capacity; more below): a
 // persistent grid of 1024-thread workgroups, one per compute unit.  A group of
 // P workgroups (1 to 8, 16 or 32: as many as hold the slice, or up to 8 where
 // few slices would leave compute units idle, see plan_k) takes one key slice
@@ -41,8 +41,13 @@
 // counted in the workspace's first word.  (Two 512-thread workgroups per
 // compute unit, each holding half as many rows, measured 1 % slower.)
 //
-// Split kernels (longer slices, or too few compute units for a group of
-// eight): a range launch over chunks of every slice, whose per-channel ranges
+// Spread groups (T past 32 workgroups' capacity, up to 256 workgroups'): the same
+// kernel with 64, 128 or 256 partners over all XCDs, a two-hop exchange, and a
+// roll call before it that hands the call to the split kernels if some
+// workgroup of the grid is not on the chip.
+//
+// Split kernels (longer slices, too few compute units for a group of eight, or
+// a spread launch that found workgroups missing): a range launch over chunks of every slice, whose per-channel ranges
 // are merged into the workspace by atomic maxima, then a code launch over
 // chunks of the image rows; each slice is read twice, but every compute unit
 // works on it.
@@ -229,21 +234,32 @@ constexpr int kPartThreads = 1024;
 constexpr int kPartWaves = kPartThreads / 64;
 // Row slots of a workgroup, in registers and in LDS, by form (16 bytes a
 // thread and slot).  The longest form holds the most rows and streams whole
-// caches; the shorter ones issue and wait for fewer loads where a workgroup
+// caches, the last one (16 slots) serves spread groups; the shorter ones issue and
+// wait for fewer loads where a workgroup
 // has fewer rows (testing each slot's use instead made every wait a full one,
 // 1346 -> 1440 us on 3584 slices of 3008 rows).
-constexpr int kPartForms = 3;
-constexpr int kPartRegSlots[kPartForms] = {15, 15, 8};
-constexpr int kPartLdsSlots[kPartForms] = {9, 0, 0};
+constexpr int kPartForms = 4;
+constexpr int kPartRegSlots[kPartForms] = {15, 15, 8, 15};
+constexpr int kPartLdsSlots[kPartForms] = {9, 0, 0, 1};
+constexpr int kSpreadForm = 3;  // used by spread groups alone
 constexpr int part_slots(int form) { return kPartRegSlots[form] + kPartLdsSlots[form]; }
 constexpr int kMaxPartners = 32;    // a group's partners share one XCD's 32 compute units
 constexpr int kSerialPartners = 8;  // up to this many, one thread per channel polls every partner
+// Spread groups (slices past kMaxPartners workgroups' capacity): 64, 128 or 256
+// partners over all XCDs.
+constexpr uint32_t kSpreadMin = 64, kSpreadMax = 256;
 // Exchange area (u64 words): a header (word 0 counts waits that ran out of
-// polls), then [group][2 buffers][partner][D] tagged words for at most
+// polls; words 1 and 2: the arrivals and the outcome of a spread launch's roll
+// call), then [group][2 buffers][partner][D] tagged words for at most
 // kExMaxWgs workgroups.
 constexpr int kExHeader = 64;
 constexpr int kExMaxWgs = 1024;
 constexpr uint32_t kSpinLimit = 1u << 20;
+constexpr int kExArrived = 1, kExOutcome = 2;
+enum : uint64_t { kUndecided = 0, kAllHere = 1, kNotAll = 2 };
+// Polls of the roll call's outcome (about 1 us each) before a workgroup closes it.
+constexpr uint32_t kRollCallPolls = 128;
+enum class Exchange { kSerial, kWide, kSpread };
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
@@ -402,14 +418,56 @@ __device__ __forceinline__ void fold_partners(const uint64_t* w, uint32_t stride
   }
 }
 
+// The roll call of a spread launch.  A spread group can only exchange when
+// every workgroup of the grid is on the chip, which another stream's kernel may
+// prevent, so the grid agrees first: the last of `expected` arrivals opens the
+// exchange, and a workgroup that has polled the outcome kRollCallPolls times
+// closes it.  One compare-and-swap decides, and nothing was published or stored
+// before it: after kNotAll every workgroup ends and the split kernels, launched
+// behind in either case, do the call's work instead.  All threads of the
+// workgroup take part (one barrier); true: every workgroup is here.
+__device__ __forceinline__ void roll_call_arrive(uint64_t* ex, uint32_t expected) {
+  const uint64_t here = __hip_atomic_fetch_add(ex + kExArrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+  if (here == expected) {
+    uint64_t want = kUndecided;
+    __hip_atomic_compare_exchange_strong(ex + kExOutcome, &want, (uint64_t)kAllHere, __ATOMIC_RELAXED,
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+__device__ __forceinline__ bool roll_call_outcome(uint64_t* ex, uint32_t* shared) {
+  if (threadIdx.x == 0) {
+    uint64_t seen = kUndecided;
+    for (uint32_t poll = 0; poll < kRollCallPolls && seen == kUndecided; ++poll) {
+      if (poll) __builtin_amdgcn_s_sleep(8);
+      seen = __hip_atomic_load(ex + kExOutcome, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (seen == kUndecided &&
+        __hip_atomic_compare_exchange_strong(ex + kExOutcome, &seen, (uint64_t)kNotAll, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      seen = kNotAll;
+    *shared = (uint32_t)seen;
+  }
+  __syncthreads();
+  return *shared == kAllHere;
+}
+
 // FORM: the row slots (kPartRegSlots, kPartLdsSlots).
-// WIDE (more than kSerialPartners partners): every thread of the workgroup
-// polls partners; else one thread per channel polls them all (its own
-// instantiation, so the common case keeps the smaller register footprint).
-template <int D, int BITS, bool FAKE, bool WIDE, int FORM>
+// EX, how the partners' ranges are exchanged (an instantiation each, so the
+// common case keeps the smaller register footprint):
+//  kSerial: one thread per channel polls every partner;
+//  kWide (more than kSerialPartners partners): every thread polls partners;
+//  kSpread (64 to 256 partners over all XCDs): all-to-all polls would read 128
+//  KiB a workgroup and slice, so partner q collects channels q, q + parts, ...
+//  (a wavefront folds 64 partners' words) and publishes what it found, and the
+//  partners poll those words, D * parts / 64 of them.  104 slices of 131072
+//  rows, 2 bits: the split kernels' 1201 us -> 974 (18.6 us a round of two
+//  slices, 10 of them their rows at the chip's rate and 5.4 the two hops and
+//  the partners' skew); whole call 2020 -> 1890.
+template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_t parts, uint32_t rows_per_part,
-                      uint64_t* __restrict__ ex) {
+                      uint32_t expected, uint64_t* __restrict__ ex) {
+  constexpr bool WIDE = EX == Exchange::kWide, SPREAD = EX == Exchange::kSpread;
   constexpr int LEVELS = (1 << BITS) - 1;
   constexpr int ROW = D * BITS / 8;
   constexpr int LR = D / 8;                  // lanes per row (8 channels each)
@@ -426,10 +484,11 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane % LR;
   const int rw = lane / LR;
-  // workgroup -> (group, partner); a group's partners are 8 workgroups apart
+  // workgroup -> (group, partner); a group's partners are 8 workgroups apart,
+  // those of a spread group follow each other
   const uint32_t bx = blockIdx.x;
-  const uint32_t q = (bx / 8u) % parts;
-  const uint32_t g = (bx / (8u * parts)) * 8u + bx % 8u;
+  const uint32_t q = SPREAD ? bx % parts : (bx / 8u) % parts;
+  const uint32_t g = SPREAD ? bx / parts : (bx / (8u * parts)) * 8u + bx % 8u;
   const int T = p.T;
   const int t_lo = (int)(q * rows_per_part);
   const int t_hi = min(t_lo + (int)rows_per_part, T);  // t_hi > t_lo (host)
@@ -499,7 +558,14 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
 #pragma unroll
     for (int k = 0; k < kRegSlots; ++k) v[k] = load_reg(r, kLdsSlots + k);
   }
-  range_pass();
+  if constexpr (SPREAD) {
+    if (tid == 0) roll_call_arrive(ex, expected);
+  }
+  range_pass();  // every load is complete, also for a workgroup that now ends
+  if constexpr (SPREAD) {
+    __shared__ uint32_t outcome;
+    if (!roll_call_outcome(ex, &outcome)) return;
+  }
 
   uint32_t seq = 0;
   for (;;) {
@@ -558,11 +624,46 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       }
       __syncthreads();
     }
+    if constexpr (SPREAD) {
+      const uint32_t gen = seq + 1;
+      const uint32_t subs = parts / 64u;  // wavefronts that fold one channel's words
+      uint64_t* buf = ex + kExHeader + ((size_t)g * 2u + (seq & 1u)) * (parts + subs) * D;  // [D][parts]
+      uint64_t* folded = buf + (size_t)parts * D;                                             // [subs][D]
+      if (tid < D)
+        __hip_atomic_store(buf + (size_t)tid * parts + q, tagged_range(red[tid], red[D + tid], gen), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t timeouts = 0;
+      {
+        const uint32_t sub = (uint32_t)wave % subs, chx = (uint32_t)wave / subs * parts + q;  // wave-uniform
+        if (chx < (uint32_t)D) {
+          float a = __builtin_inff(), b = -__builtin_inff();
+          fold_partner(buf + (size_t)chx * parts + sub * 64u + lane, gen, a, b, timeouts);
+#pragma unroll
+          for (int off = 1; off < 64; off *= 2) {
+            a = fminf(a, __shfl_xor(a, off));
+            b = fmaxf(b, __shfl_xor(b, off));
+          }
+          if (lane == 0)
+            __hip_atomic_store(folded + (size_t)sub * D + chx, tagged_range(a, b, gen), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+      if ((uint32_t)tid < subs * D) {
+        float a = __builtin_inff(), b = -__builtin_inff();
+        fold_partner(folded + tid, gen, a, b, timeouts);
+        if (a <= b) {
+          atomicMin(&red[tid % D], a);
+          atomicMax(&red[D + tid % D], b);
+        }
+      }
+      if (timeouts) __hip_atomic_fetch_add(ex, (uint64_t)timeouts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+    }
     if (tid < D) {
       float a = red[tid], b = red[D + tid];
       red[tid] = __builtin_inff();  // reset for the next slice (several barriers away)
       red[D + tid] = -__builtin_inff();
-      if (!WIDE && parts > 1) {
+      if (EX == Exchange::kSerial && parts > 1) {
         const uint32_t gen = seq + 1;
         uint64_t* buf = ex + kExHeader + ((size_t)g * 2u + (seq & 1u)) * parts * D;
         __hip_atomic_store(buf + (size_t)q * D + tid, tagged_range(a, b, gen), __ATOMIC_RELAXED,
@@ -699,75 +800,96 @@ __device__ __forceinline__ float from_ord_image(uint32_t o) {
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o);
 }
 
-template <int D>
+// Both launches take `blocks` (slice, chunk) pairs, a workgroup each, or, behind
+// a spread launch (GUARDED; `outcome`: its roll call's word), kGuardedBlocks
+// workgroups walk them, and none where the spread kernel has done the work.  (An
+// instantiation each: the loop costs the plain launches 1 %.)
+
+constexpr uint32_t kGuardedBlocks = 1024;  // four workgroups per compute unit
+
+template <int D, bool GUARDED>
 __global__ __launch_bounds__(kSplitThreads) void kivi_split_range_kernel(const Params p, uint32_t item0,
                                                                          uint32_t n_items, uint32_t chunks,
+                                                                         uint32_t blocks,
+                                                                         const uint64_t* __restrict__ outcome,
                                                                          uint32_t* __restrict__ words) {
-  constexpr int CPT = D / 8;
-  __shared__ float red[2 * D];
-  const int tid = threadIdx.x;
-  const uint32_t local = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
-  const ResItem it = res_item(p, item0 + local, n_items);  // valid: the grid covers the batch exactly
-  for (int i = tid; i < 2 * D; i += kSplitThreads) red[i] = i < D ? __builtin_inff() : -__builtin_inff();
-  __syncthreads();
-  const int t_begin = (int)chunk * kSplitRows;
-  const int t_end = min(p.T, t_begin + kSplitRows);
-  float mn[8], mx[8];
-  range_rows<D, kSplitWaves, kSplitRangeUnroll>(p.cache[0] + (size_t)it.s * p.T * D, t_begin, t_end, mn, mx);
-  const int lane = tid & 63;
-  if (lane < CPT) {
+  if (GUARDED && *outcome == kAllHere) return;
+  for (uint32_t bx = blockIdx.x; bx < blocks; bx += gridDim.x) {
+    constexpr int CPT = D / 8;
+    __shared__ float red[2 * D];
+    const int tid = threadIdx.x;
+    const uint32_t local = bx / chunks, chunk = bx % chunks;
+    const ResItem it = res_item(p, item0 + local, n_items);  // valid: the grid covers the batch exactly
+    for (int i = tid; i < 2 * D; i += kSplitThreads) red[i] = i < D ? __builtin_inff() : -__builtin_inff();
+    __syncthreads();
+    const int t_begin = (int)chunk * kSplitRows;
+    const int t_end = min(p.T, t_begin + kSplitRows);
+    float mn[8], mx[8];
+    range_rows<D, kSplitWaves, kSplitRangeUnroll>(p.cache[0] + (size_t)it.s * p.T * D, t_begin, t_end, mn, mx);
+    const int lane = tid & 63;
+    if (lane < CPT) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      atomicMin(&red[8 * lane + e], mn[e]);
-      atomicMax(&red[D + 8 * lane + e], mx[e]);
+      for (int e = 0; e < 8; ++e) {
+        atomicMin(&red[8 * lane + e], mn[e]);
+        atomicMax(&red[D + 8 * lane + e], mx[e]);
+      }
     }
-  }
-  __syncthreads();
-  if (tid < D) {
-    uint32_t* w = words + (size_t)local * 2 * D;
-    __hip_atomic_fetch_max(w + tid, ~ord_image(red[tid]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_max(w + D + tid, ord_image(red[D + tid]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (tid < D) {
+      uint32_t* w = words + (size_t)local * 2 * D;
+      __hip_atomic_fetch_max(w + tid, ~ord_image(red[tid]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(w + D + tid, ord_image(red[D + tid]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!GUARDED) return;
+    __syncthreads();  // the next pair's ranges reuse `red`
   }
 }
 
-template <int D, int BITS, bool FAKE>
+template <int D, int BITS, bool FAKE, bool GUARDED>
 __global__ __launch_bounds__(kSplitThreads) void kivi_split_code_kernel(const Params p, uint32_t item0,
                                                                         uint32_t n_items, uint32_t chunks,
+                                                                        uint32_t blocks,
+                                                                        const uint64_t* __restrict__ outcome,
                                                                         const uint32_t* __restrict__ words) {
-  constexpr int CPT = D / 8;
-  constexpr int LEVELS = (1 << BITS) - 1;
-  constexpr int ROW = D * BITS / 8;
-  __shared__ uint32_t g_meta[D];
-  __shared__ float g_inv[D];
-  const int tid = threadIdx.x;
-  const uint32_t local = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
-  const uint32_t item = item0 + local;
-  const ResItem it = res_item(p, item, n_items);
-  const size_t slab = (size_t)item;  // [slot][B] with slot = item / B
-  if (tid < D) {
-    const uint32_t* w = words + (size_t)local * 2 * D;
-    const GroupScale gs = group_scale<LEVELS>(from_ord_image(~w[tid]), from_ord_image(w[D + tid]));
-    g_meta[tid] = gs.meta;
-    g_inv[tid] = gs.inv;
-    if (!FAKE && chunk == 0) __builtin_nontemporal_store(gs.meta, p.meta[0] + slab * D + tid);
-  }
-  __syncthreads();
-  const int c8 = (tid & 63) % CPT;
-  GroupScale g[8];
-  float S[8];
+  if (GUARDED && *outcome == kAllHere) return;
+  for (uint32_t bx = blockIdx.x; bx < blocks; bx += gridDim.x) {
+    constexpr int CPT = D / 8;
+    constexpr int LEVELS = (1 << BITS) - 1;
+    constexpr int ROW = D * BITS / 8;
+    __shared__ uint32_t g_meta[D];
+    __shared__ float g_inv[D];
+    const int tid = threadIdx.x;
+    const uint32_t local = bx / chunks, chunk = bx % chunks;
+    const uint32_t item = item0 + local;
+    const ResItem it = res_item(p, item, n_items);
+    const size_t slab = (size_t)item;  // [slot][B] with slot = item / B
+    if (tid < D) {
+      const uint32_t* w = words + (size_t)local * 2 * D;
+      const GroupScale gs = group_scale<LEVELS>(from_ord_image(~w[tid]), from_ord_image(w[D + tid]));
+      g_meta[tid] = gs.meta;
+      g_inv[tid] = gs.inv;
+      if (!FAKE && chunk == 0) __builtin_nontemporal_store(gs.meta, p.meta[0] + slab * D + tid);
+    }
+    __syncthreads();
+    const int c8 = (tid & 63) % CPT;
+    GroupScale g[8];
+    float S[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    g[e].meta = g_meta[8 * c8 + e];
-    g[e].m = bf16_as_float(g[e].meta >> 16);
-    g[e].inv = g_inv[8 * c8 + e];
-    S[e] = bf16_as_float(g[e].meta & 0xFFFFu);
+    for (int e = 0; e < 8; ++e) {
+      g[e].meta = g_meta[8 * c8 + e];
+      g[e].m = bf16_as_float(g[e].meta >> 16);
+      g[e].inv = g_inv[8 * c8 + e];
+      S[e] = bf16_as_float(g[e].meta & 0xFFFFu);
+    }
+    const int t_begin = (int)chunk * kSplitRows;
+    const int t_end = min(p.n, t_begin + kSplitRows);
+    code_rows<D, BITS, FAKE, kSplitWaves, kSplitCodeUnroll>(p.cache[0] + ((size_t)it.s * p.T + p.s0) * D,
+                                          FAKE ? nullptr : p.codes[0] + slab * p.n * ROW,
+                                          FAKE ? p.out[0] + ((size_t)it.s * p.T + p.s0) * D : nullptr, t_begin, t_end,
+                                          g, S);
+    if (!GUARDED) return;
+    __syncthreads();  // the next pair's scales reuse g_meta and g_inv
   }
-  const int t_begin = (int)chunk * kSplitRows;
-  const int t_end = min(p.n, t_begin + kSplitRows);
-  code_rows<D, BITS, FAKE, kSplitWaves, kSplitCodeUnroll>(p.cache[0] + ((size_t)it.s * p.T + p.s0) * D,
-                                        FAKE ? nullptr : p.codes[0] + slab * p.n * ROW,
-                                        FAKE ? p.out[0] + ((size_t)it.s * p.T + p.s0) * D : nullptr, t_begin, t_end,
-                                        g, S);
 }
 
 // Zeroes the exchange words a launch uses (a kernel rather than a memset, so
@@ -821,9 +943,11 @@ static hipError_t grid_cus(int* cus) {
 // workspace words to clear before it (the exchange words the resident grid
 // uses, or the header and the first batch's range words: the split kernels
 // wait for nothing, so the header's first word then reads 0).
+// A spread plan (`spread`) has both: its roll call picks one on the device.
 struct KiviPlan {
   bool resident = false;
   bool split = false;
+  bool spread = false;
   int parts = 0;
   int form = 0;
   uint32_t n_items = 0, groups = 0, rows_per_part = 0;
@@ -859,7 +983,7 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   const uint32_t fewest = (uint32_t)kivi_partners(p.T, D);
   const uint32_t most = has_ws ? std::max(fewest, (uint32_t)kSerialPartners) : 1u;
   uint64_t best = ~0ull;
-  for (int form = 0; form < kPartForms && fewest > 0; ++form) {
+  for (int form = 0; form < kSpreadForm && fewest > 0; ++form) {
     for (uint32_t parts = fewest; parts <= most; ++parts) {
       const uint32_t cap = wgs / parts / 8u * 8u;  // groups held at once
       const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
@@ -886,17 +1010,70 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
     }
   }
   if (pl->resident) return hipSuccess;
+  // Slices past kMaxPartners workgroups: a spread group reads each slice once
+  // where the split kernels read it twice.  By the same count, a round's
+  // exchange takes 250 (two hops, and no loads in flight); the split kernels
+  // take 2.2 times the chip's time of every slice, and 500 for the second
+  // launch and the last chunks.  Split -> spread, whole calls (us, 2 bits,
+  // head_dim 128): slices of 131072 rows, 2 57.5 -> 51.3, 3 84 -> 85, 104 2072 ->
+  // 1879 (one-pass 3130 -> 2991); 17 of 100000 309 -> 293; one of 50000 33.9 ->
+  // 27.3; 7 of 300000 366 -> 334; 2 of 200000 71 -> 73.
+  const uint64_t per_slot = (uint64_t)(kPartWaves * (512 / D));
+  auto chip = [&](uint64_t active) { return 20u * active * (uint64_t)p.T / (per_slot * wgs); };
+  best = chip(11ull * pl->n_items) / 5u + 500u;
+  for (uint32_t parts = kSpreadMin; has_ws && parts <= kSpreadMax; parts *= 2) {
+    const uint32_t groups = std::min(pl->n_items, std::min(wgs, (uint32_t)kExMaxWgs / 2) / parts);  // fits the area
+    const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
+    if (groups == 0 || (uint64_t)p.T * D * 2 >= (1ull << 31)) continue;
+    if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;  // every partner has a row
+    const uint32_t rounds = (pl->n_items + groups - 1) / groups;
+    const uint32_t used = (uint32_t)((rows + per_slot - 1) / per_slot);
+    for (int form : {2, kSpreadForm, 0}) {
+      if (used > (uint32_t)part_slots(form)) continue;  // every row fits a slot
+      auto round_cost = [&](uint64_t active) {
+        return std::max<uint64_t>(11u * used, chip(active)) + 7u * ((uint32_t)part_slots(form) - used) + 250u;
+      };
+      const uint64_t cost = (rounds - 1) * round_cost(groups) + round_cost(pl->n_items - (rounds - 1) * groups) + 150u;
+      if (cost >= best) continue;
+      best = cost;
+      pl->resident = pl->spread = true;
+      pl->form = form;
+      pl->parts = (int)parts;
+      pl->groups = groups;
+      pl->rows_per_part = rows;
+      pl->clear_words = (uint32_t)(kExHeader + (uint64_t)groups * 2 * (parts + parts / 64) * D);
+    }
+  }
   if (has_ws) {
     pl->split = true;
-    pl->clear_words = (uint32_t)(kExHeader + (uint64_t)std::min(pl->n_items, kSplitBatch) * D);
+    pl->clear_words = std::max(pl->clear_words, (uint32_t)(kExHeader + (uint64_t)std::min(pl->n_items, kSplitBatch) * D));
   }
   return hipSuccess;
 }
 
-template <int D, int BITS, bool FAKE, bool WIDE, int FORM>
+// Test hook: with HG_TEST_ABSENT=n in the environment a spread launch's roll
+// call waits for n workgroups that do not exist, so the split kernels do the work.
+static uint32_t absent_workgroups() {
+  const char* s = getenv("HG_TEST_ABSENT");
+  return s && *s ? (uint32_t)std::max(0, atoi(s)) : 0u;
+}
+
+template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 static void launch_part(const Params& p, const KiviPlan& pl, void* ws, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, WIDE, FORM>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
-                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part, (uint64_t*)ws);
+  hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, EX, FORM>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
+                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part,
+                     EX == Exchange::kSpread ? grid.x + absent_workgroups() : 0u, (uint64_t*)ws);
+}
+
+// The range and code launches of `nb` slices.
+template <int D, int BITS, bool FAKE, bool GUARDED>
+static void launch_split(const Params& p, uint32_t i0, uint32_t nb, uint32_t n_items, uint32_t range_chunks,
+                         uint32_t code_chunks, const uint64_t* outcome, uint32_t* words, hipStream_t stream) {
+  auto grid = [](uint32_t blocks) { return dim3(GUARDED ? std::min(blocks, kGuardedBlocks) : blocks); };
+  hipLaunchKernelGGL((kivi_split_range_kernel<D, GUARDED>), grid(nb * range_chunks), dim3(kSplitThreads), 0, stream, p,
+                     i0, n_items, range_chunks, nb * range_chunks, outcome, words);
+  hipLaunchKernelGGL((kivi_split_code_kernel<D, BITS, FAKE, GUARDED>), grid(nb * code_chunks), dim3(kSplitThreads), 0,
+                     stream, p, i0, n_items, code_chunks, nb * code_chunks, outcome, (const uint32_t*)words);
 }
 
 template <int D, int BITS, bool FAKE>
@@ -913,19 +1090,25 @@ static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t 
   if (pl.resident) {
     const dim3 grid(pl.groups * (uint32_t)pl.parts);
     const bool wide = pl.parts > kSerialPartners;
-    if (pl.form == 0)
-      wide ? launch_part<D, BITS, FAKE, true, 0>(p, pl, ws, grid, stream)
-           : launch_part<D, BITS, FAKE, false, 0>(p, pl, ws, grid, stream);
+    if (pl.spread)
+      pl.form == 0   ? launch_part<D, BITS, FAKE, Exchange::kSpread, 0>(p, pl, ws, grid, stream)
+      : pl.form == 2 ? launch_part<D, BITS, FAKE, Exchange::kSpread, 2>(p, pl, ws, grid, stream)
+                     : launch_part<D, BITS, FAKE, Exchange::kSpread, kSpreadForm>(p, pl, ws, grid, stream);
+    else if (pl.form == 0)
+      wide ? launch_part<D, BITS, FAKE, Exchange::kWide, 0>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, Exchange::kSerial, 0>(p, pl, ws, grid, stream);
     else if (pl.form == 1)
-      wide ? launch_part<D, BITS, FAKE, true, 1>(p, pl, ws, grid, stream)
-           : launch_part<D, BITS, FAKE, false, 1>(p, pl, ws, grid, stream);
+      wide ? launch_part<D, BITS, FAKE, Exchange::kWide, 1>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, Exchange::kSerial, 1>(p, pl, ws, grid, stream);
     else
-      wide ? launch_part<D, BITS, FAKE, true, 2>(p, pl, ws, grid, stream)
-           : launch_part<D, BITS, FAKE, false, 2>(p, pl, ws, grid, stream);
-    return hipGetLastError();
+      wide ? launch_part<D, BITS, FAKE, Exchange::kWide, 2>(p, pl, ws, grid, stream)
+           : launch_part<D, BITS, FAKE, Exchange::kSerial, 2>(p, pl, ws, grid, stream);
+    e = hipGetLastError();
+    if (e != hipSuccess || !pl.spread) return e;
   }
   if (pl.split) {
     uint32_t* words = (uint32_t*)((uint64_t*)ws + kExHeader);
+    const uint64_t* outcome = pl.spread ? (const uint64_t*)ws + kExOutcome : nullptr;
     const uint32_t range_chunks = (uint32_t)((p.T + kSplitRows - 1) / kSplitRows);
     const uint32_t code_chunks = (uint32_t)((p.n + kSplitRows - 1) / kSplitRows);
     // slices per launch pair: the words area's, and few enough that a launch
@@ -940,10 +1123,10 @@ static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t 
         hipLaunchKernelGGL(zero_words_kernel, dim3(std::min<uint32_t>((n64 + 255) / 256, 1024)), dim3(256), 0, stream,
                            (uint64_t*)words, n64);
       }
-      hipLaunchKernelGGL((kivi_split_range_kernel<D>), dim3(nb * range_chunks), dim3(kSplitThreads), 0, stream, p, i0,
-                         pl.n_items, range_chunks, words);
-      hipLaunchKernelGGL((kivi_split_code_kernel<D, BITS, FAKE>), dim3(nb * code_chunks), dim3(kSplitThreads), 0,
-                         stream, p, i0, pl.n_items, code_chunks, (const uint32_t*)words);
+      if (pl.spread)
+        launch_split<D, BITS, FAKE, true>(p, i0, nb, pl.n_items, range_chunks, code_chunks, outcome, words, stream);
+      else
+        launch_split<D, BITS, FAKE, false>(p, i0, nb, pl.n_items, range_chunks, code_chunks, nullptr, words, stream);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

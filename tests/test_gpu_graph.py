@@ -4,7 +4,7 @@ and in place) is captured once (the calls only launch kernels on the given
 stream: no allocation, no synchronisation, no memset) and replayed several
 times, with the outputs cleared by eager work in between; every replay must
 write exactly the bytes of the eager calls.  Covers the per-token, KIVI
-(grouped and whole-sequence, with one, 2 and 16 workgroups per slice) and
+(grouped and whole-sequence, with one, 2, 16 and 128 workgroups per slice) and
 AKVQ-with-retention paths."""
 import numpy as np
 import pytest
@@ -21,6 +21,8 @@ CASES = [small("minmax", img_len=300), small("kivi", keys_only=1, img_len=300),
          # exchange words cleared inside the graph on every replay)
          small("kivi", img_len=3000, H=2).with_(kivi_group=0, name="kivi-whole-2-partners"),
          small("kivi", img_len=12500, L=1, H=2, n_protected=1).with_(kivi_group=0, name="kivi-whole-16-partners"),
+         # a spread group, its roll call's words cleared on every replay too
+         small("kivi", img_len=50000, L=1, H=2, n_protected=1).with_(kivi_group=0, name="kivi-whole-spread-partners"),
          small("akvq", img_len=300).with_(retain_permille=50, name="akvq-retain")]
 
 

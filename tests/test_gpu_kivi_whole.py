@@ -8,7 +8,9 @@ Slices of up to 32 workgroups' capacity (24 slots of 8192/D rows: 3072,
 1536 and 768 rows at head_dim 64, 128 and 256) go through the partitioned
 resident kernel: P workgroups each hold a run of a slice's rows on chip and
 combine their partial ranges through the call's workspace (past 8, P is
-rounded up to 16 or 32); longer slices go through the split kernels (a
+rounded up to 16 or 32); longer slices, up to 256 workgroups' capacity, go
+through spread groups of 64, 128 or 256 workgroups if a roll call finds the
+whole grid on the chip, and else, like still longer ones, through the split kernels (a
 range launch over chunks of every slice merging per-channel ranges into the
 workspace, then a code launch), and a slice one workgroup holds, on a device
 too small for a group, through the two-pass kernel (no workspace).
@@ -210,6 +212,80 @@ def test_capacity_boundary_fake(T, inplace):
               L=1, B=2, H=2, n_protected=1).with_(kivi_group=0)
     K, V = synthkv.gen_kv(w)
     check_fake(w, K, V, synthkv.protect_mask(w), inplace)
+
+
+# Spread groups: slices past 32 workgroups' capacity, at the capacities of 64,
+# 128 and 256 workgroups of 8, 16 and 24 slots and one row past them, one round
+# and several (the grid hook: 64 and 128 compute units hold one group of 64, one
+# of 128).  `outcome` is what the roll call decides: every workgroup is here, or
+# (HG_TEST_ABSENT waits for one that does not exist) the split kernels do the
+# work, or no roll call (past the capacity).
+def _spread_cases():
+    out = []
+    for D in (64, 128, 256):
+        r = 8192 // D
+        out += [(D, "", 32 * 24 * r + 1, 4), (D, "", 64 * 16 * r, 4), (D, "128", 64 * 16 * r + 1, 4),
+                (D, "64", 64 * 24 * r, 4), (D, "", 64 * 24 * r + 1, 4), (D, "", 128 * 8 * r + 1, 1)]
+    out += [(256, "128", 128 * 16 * 32, 4), (256, "", 128 * 16 * 32 + 1, 4), (256, "", 256 * 8 * 32, 1),
+            (256, "", 256 * 24 * 32, 1), (256, "", 256 * 24 * 32 + 1, 1)]
+    return out
+
+
+def _spread_workload(D, T, H, bits=2):
+    w = small("kivi", D, bits, 1, img_len=T - 700, img_start=300, text=400, L=1, B=1, H=H,
+              n_protected=1 if H > 1 else 0).with_(kivi_group=0, name=f"kiviseq-spread-D{D}-T{T}")
+    assert w.T == T
+    K, V = synthkv.gen_kv(w)
+    K[0, :, :, T - 1, 5] = -4000.0  # extremes in the last and first rows
+    K[0, :, :, 0, 9] = 5000.0
+    return w, K, V, synthkv.protect_mask(w)
+
+
+@pytest.mark.parametrize("D,cus,T,H", _spread_cases(), ids=lambda v: str(v) or "all")
+@pytest.mark.parametrize("absent", ["", "1"])
+def test_spread_groups(D, cus, T, H, absent, monkeypatch):
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    monkeypatch.setenv("HG_TEST_ABSENT", absent)
+    w, K, V, mask = _spread_workload(D, T, H, bits=3 if D == 64 else 2)
+    ws = []
+
+    def prefill(pk):
+        _stale_words(pk["workspace"])
+        ws.append(pk["workspace"])
+    _assert_exact(compare_full(w, K, V, mask, prefill=prefill), w.name)
+    outcome = int(ws[0][16:24].cpu().numpy().view(np.uint64)[0])
+    assert outcome == (0 if T > 256 * capacity(D) else 2 if absent else 1)
+
+
+@pytest.mark.parametrize("T,H", [(65536, 4), (98305, 3), (131072, 1)])
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("absent", ["", "1"])
+def test_spread_groups_fake(T, H, inplace, absent, monkeypatch):
+    monkeypatch.setenv("HG_TEST_ABSENT", absent)
+    w, K, V, mask = _spread_workload(128, T, H)
+    check_fake(w, K, V, mask, inplace, prefill_ws=_stale_words)
+
+
+def test_spread_groups_share_the_chip():
+    """Two calls whose grids each want every compute unit, on two streams: the
+    roll call of either may find workgroups missing and leave its work to the
+    split kernels; the packed bytes are those of a call alone."""
+    import paper_2609_35800_amd as hg
+    w, K, V, mask = _spread_workload(128, 65536, 4)
+    cfg = hg.make_config(**w.config_fields())
+    Kg, Vg = K.cuda(), V.cuda()
+    want = hg.alloc_packed(cfg, mask)
+    hg.hg_quantize(cfg, Kg, Vg, mask, want)
+    packed = [hg.alloc_packed(cfg, mask) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for s, pk in zip(streams, packed):
+            hg.hg_quantize(cfg, Kg, Vg, mask, pk, stream=s)
+    torch.cuda.synchronize()
+    for pk in packed:
+        assert int(pk["workspace"][:8].view(torch.int64)[0]) == 0
+        assert all(torch.equal(pk[n], want[n]) for n in hg.BUFFERS)
 
 
 @pytest.mark.parametrize("which", ["none", "all", "last"])
