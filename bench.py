@@ -41,7 +41,7 @@ KERNEL_SOURCES = {
     FAKE_KERNEL: tuple(_CSRC + f for f in ("fakequant.hip", "hg_device.h", "hg_kernels.h")),
 }
 KIVI_WHOLE_SOURCE = _CSRC + "kivi_seq.hip"
-RETAIN_SOURCE = _CSRC + "retain.hip"
+RETAIN_SOURCES = (_CSRC + "retain.hip", _CSRC + "hg_retain.h")
 # The measured-results table: the five workloads (the 72B-shaped one at each
 # bit width), the whole-sequence KIVI keys, the 2 % token retention and a
 # 128K-token context with whole-sequence keys, each as a quantize + dequantize
@@ -153,7 +153,7 @@ def kernel_sources(kernel: str, w=None) -> tuple:
     if kernel in (QUANT_KERNEL, FAKE_KERNEL) and kivi_whole:
         srcs.append(KIVI_WHOLE_SOURCE)
     if w is None or w.retain_permille:
-        srcs.append(RETAIN_SOURCE)
+        srcs.extend(RETAIN_SOURCES)
     return tuple(srcs)
 
 
