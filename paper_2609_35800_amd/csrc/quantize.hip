@@ -336,12 +336,18 @@ static size_t values_select_lds(int bits) {
 
 // Spans whose norms fit that LDS (6000 tokens at 2 bits and head_dim 128; 3900
 // at head_dim 256): a larger reservation would cost the value tiles their
-// occupancy, so longer spans select in a launch of their own.
-bool select_with_values(const Params& p, int D, int bits) {
+// occupancy, so longer spans select in a launch of their own.  So do slices so
+// many and short that the launch, one workgroup a slice longer than that of the
+// values alone, would have 2^32 work-items or more, which the runtime refuses.
+static bool select_fits(uint64_t slices, uint64_t n, int D, int bits) {
   const size_t lds = D == 64 ? values_select_lds<64>(bits) : D == 128 ? values_select_lds<128>(bits)
                                                                       : values_select_lds<256>(bits);
-  const uint64_t blocks = (uint64_t)p.L * p.B * p.H * ((uint64_t)(p.n + kBlockTokens - 1) / kBlockTokens + 1);
-  return p.k > 0 && (size_t)p.n * sizeof(uint32_t) <= lds && blocks <= 0x7FFFFFFFull;
+  const uint64_t blocks = slices * ((n + kBlockTokens - 1) / kBlockTokens + 1);
+  return n * sizeof(uint32_t) <= lds && blocks <= 0xFFFFFFFFull / kThreads;
+}
+
+bool select_with_values(const Params& p, int D, int bits) {
+  return p.k > 0 && select_fits((uint64_t)p.L * p.B * p.H, (uint64_t)p.n, D, bits);
 }
 
 template <int D, int BITS>
@@ -448,3 +454,8 @@ hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norm
 }
 
 }  // namespace hg
+
+// Host-only query for the tests of the rule above (not part of headguard.h).
+extern "C" int hg_test_select_with_values(uint64_t slices, uint64_t n, int D, int bits) {
+  return hg::select_fits(slices, n, D, bits);
+}

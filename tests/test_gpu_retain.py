@@ -233,3 +233,22 @@ def test_full_size_internvl_two_percent():
 def test_full_size_internvl_two_percent_one_pass(inplace):
     w = synthkv.WORKLOADS["internvl-8b"].with_(retain_permille=20)
     wholecache.assert_whole(wholecache.fake_quantize(w, inplace=inplace), w)
+
+
+def test_many_short_slices():
+    """2^23 slices of one token, all retained: the values' launch alone is half of
+    what one launch can have, so the selection has to follow in a launch of its
+    own.  Every row is stored in BF16, so quantize and dequantize give K and V."""
+    import paper_2609_35800_amd as hg
+    cfg = hg.make_config(L=64, B=1024, H=128, T=1, D=64, img_start=0, img_len=1, bits=2, base="akvq", keys_only=1,
+                         retain_permille=1000)
+    mask = np.zeros(64 * 128, np.uint8)
+    mask[5::8] = 1
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn((64, 1024, 128, 1, 64), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    packed = hg.alloc_packed(cfg, mask)
+    hg.hg_quantize(cfg, K, V, mask, packed)
+    assert not packed["ret_idx"].view(torch.int32).any()
+    Ko, Vo = torch.zeros_like(K), torch.zeros_like(V)
+    hg.hg_dequantize(cfg, mask, packed, Ko, Vo)
+    assert torch.equal(Ko, K) and torch.equal(Vo, V)
