@@ -35,9 +35,12 @@
 //     reconstruction) of the workgroup's image rows: whole packed rows, so
 //     every stored line is complete; as the row slots are consumed, the
 //     loads of the workgroup's rows of the next slice are issued into them.
-// The grid never exceeds the number of workgroups the device holds at once,
-// so every partner of a group is resident; a wait that runs out of polls
-// (only if another kernel held the device's resources) ends anyway and is
+// The grid never exceeds the number of workgroups the device holds at once, so
+// every partner of a group is resident unless another kernel holds compute
+// units.  The partners of a group therefore agree first that all of them are on
+// the chip (see close_partner); if they are not, those that are take the group's
+// slices one workgroup a slice (slice_alone), which waits for nobody.  A wait
+// after the agreement still ends after a bounded number of polls and is then
 // counted in the workspace's first word.  (Two 512-thread workgroups per
 // compute unit, each holding half as many rows, measured 1 % slower.)
 //
@@ -79,17 +82,17 @@ constexpr int kSeqUnroll2 = 4;  // rows in flight per lane, code pass
 // Per-channel range, over rows [t_begin, t_end) of a slice, of the 8
 // channels this lane loads (lane i: channels 8 (i % (D/8)) on, row i / (D/8)
 // of each WAVES * 64 / (D/8) rows), reduced over the wavefront's rows by
-// shuffles; rows past the end re-read the last row, which leaves the range
+// shuffles (not without ACROSS); rows past the end re-read the last row, which leaves the range
 // unchanged.  t_end > t_begin.  Streaming loads, here and in code_rows (9 %
 // and 3 % faster launches than cached loads).
-template <int D, int WAVES, int U = kSeqUnroll1>
+template <int D, int WAVES, int U = kSeqUnroll1, bool ACROSS = true>
 __device__ __forceinline__ void range_rows(const uint16_t* __restrict__ slice, int t_begin, int t_end, float (&mn)[8],
-                                           float (&mx)[8]) {
+                                           float (&mx)[8], int tid = threadIdx.x) {
   constexpr int CPT = D / 8;
   constexpr int RPL = 64 / CPT;
   constexpr int STEP = WAVES * RPL;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c8 = lane % CPT;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -112,6 +115,7 @@ __device__ __forceinline__ void range_rows(const uint16_t* __restrict__ slice, i
       }
     }
   }
+  if (!ACROSS) return;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
 #pragma unroll
@@ -128,13 +132,14 @@ __device__ __forceinline__ void range_rows(const uint16_t* __restrict__ slice, i
 // scales g (S: the scales as floats).  t_end > t_begin.
 template <int D, int BITS, bool FAKE, int WAVES, int U = kSeqUnroll2>
 __device__ __forceinline__ void code_rows(const uint16_t* __restrict__ rows, uint8_t* codes, uint16_t* out,
-                                          int t_begin, int t_end, const GroupScale (&g)[8], const float (&S)[8]) {
+                                          int t_begin, int t_end, const GroupScale (&g)[8], const float (&S)[8],
+                                          int tid = threadIdx.x) {
   constexpr int CPT = D / 8;
   constexpr int RPL = 64 / CPT;
   constexpr int STEP = WAVES * RPL;
   constexpr int ROW = D * BITS / 8;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c8 = lane % CPT;
   for (int t0 = t_begin + wave * RPL + lane / CPT; t0 < t_end; t0 += U * STEP) {
     u32x4 v[U];
@@ -250,13 +255,20 @@ constexpr int kSerialPartners = 8;  // up to this many, one thread per channel p
 constexpr uint32_t kSpreadMin = 64, kSpreadMax = 256;
 // Exchange area (u64 words): a header (word 0 counts waits that ran out of
 // polls; words 1 and 2: the arrivals and the outcome of a spread launch's roll
-// call), then [group][2 buffers][partner][D] tagged words for at most
-// kExMaxWgs workgroups.
+// call; word 3 counts the partners closed, see close_partner), then [group][2
+// buffers][partner][D] tagged words and [group][1 + partner] words of the groups'
+// agreements (spread groups: [group][2][D (partners + partners / 64)] words) for
+// at most kExMaxWgs workgroups; the area has room for twice as many tagged words.
 constexpr int kExHeader = 64;
-constexpr int kExMaxWgs = 1024;
+constexpr int kExAreaWgs = 1024;
+constexpr int kExMaxWgs = kExAreaWgs / 2;
 constexpr uint32_t kSpinLimit = 1u << 20;
-constexpr int kExArrived = 1, kExOutcome = 2;
+constexpr int kExArrived = 1, kExOutcome = 2, kExClosed = 3;
 enum : uint64_t { kUndecided = 0, kAllHere = 1, kNotAll = 2 };
+// Polls of a partner's first word (about 1 us each) before the partner is closed:
+// long enough to wait for a short kernel of another stream, whose compute units
+// the missing partners then take.
+constexpr uint32_t kGroupPolls = 512;
 // Polls of the roll call's outcome (about 1 us each) before a workgroup closes it.
 constexpr uint32_t kRollCallPolls = 128;
 enum class Exchange { kSerial, kWide, kSpread };
@@ -363,58 +375,84 @@ __device__ __forceinline__ uint64_t tagged_range(float lo, float hi, uint32_t ge
   return ((uint64_t)gen << 32) | (__float_as_uint(hi) & 0xFFFF0000u) | (__float_as_uint(lo) >> 16);
 }
 
-// Folds partner r's range of one channel into [a, b]: `w` is the partner's
-// word of the channel, loaded again, with a short sleep, until it carries
-// tag `gen` or kSpinLimit polls have passed (then counted).  One word per
-// partner and round trip: the minimum and the maximum arrive together.
-__device__ __forceinline__ void fold_partner(const uint64_t* w, uint32_t gen, float& a, float& b,
-                                             uint32_t& timeouts) {
-  uint64_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (uint32_t spin = 0; (uint32_t)(v >> 32) != gen; ++spin) {
-    if (spin == kSpinLimit) {
-      ++timeouts;
-      return;
-    }
+// The agreement of a group's partners that all of them are on the chip.  A
+// partner only runs once a compute unit is free for it, and other kernels, among
+// them groups of other calls that wait for partners of their own, may hold those,
+// so a partner that is not here cannot be waited for without end.  Each partner
+// has a word, which it turns from 0 to kHere by a compare-and-swap before it
+// publishes its first range, and which another one that has polled in vain for
+// that range turns to kClosed by the same means, so either the one or the other
+// happens.  A partner that sees the first ranges of all the others knows that all
+// are here for good; with one of them closed no partner ever sees them all, and
+// each finds that out by its own polls.  Nothing is stored before the first
+// exchange, so the partners of such a group, those that come late too, then take
+// its slices one at a time from the group's counter, a workgroup a slice, which
+// waits for nobody.  (Calls of one round with the agreement take 0.3 to 0.6 us
+// more than without; 3584 slices of 3008 rows the same.)
+constexpr uint64_t kHere = 1, kClosed = 2;
+__device__ __forceinline__ bool close_partner(uint64_t* word, uint64_t* ex) {
+  uint64_t seen = 0;
+  if (!__hip_atomic_compare_exchange_strong(word, &seen, kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT))
+    return seen == kClosed;
+  __hip_atomic_fetch_add(ex + kExClosed, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// Loads a partner's word again, with a short sleep, until it carries tag `gen`;
+// `v`: its value as loaded before.  False after `limit` polls.
+__device__ __forceinline__ bool await_word(const uint64_t* w, uint64_t& v, uint32_t gen, uint32_t limit) {
+  uint32_t spin = 0;
+  while ((uint32_t)(v >> 32) != gen && spin < limit) {
     __builtin_amdgcn_s_sleep(2);
     v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ++spin;
   }
+  return (uint32_t)(v >> 32) == gen;
+}
+
+// A published range folded into [a, b]: the minimum and the maximum arrive together.
+__device__ __forceinline__ void fold_word(uint64_t v, float& a, float& b) {
   a = fminf(a, __uint_as_float((uint32_t)v << 16));
   b = fmaxf(b, __uint_as_float((uint32_t)v & 0xFFFF0000u));
 }
 
-// The same for partners first, first + step, ... (below parts, without q):
-// `w` is partner 0's word of the channel, the partners' words stride words
-// apart.  The words of N partners are loaded together, so they cost one round
-// trip (28 slices of 8 workgroups in place 23.3 -> 21.9 us).
-template <int N>
-__device__ __forceinline__ void fold_partners(const uint64_t* w, uint32_t stride, uint32_t first, uint32_t step,
-                                              uint32_t parts, uint32_t q, uint32_t gen, float& a, float& b,
-                                              uint32_t& timeouts) {
-  for (uint32_t r0 = first; r0 < parts; r0 += N * step) {
-    uint64_t v[N];
+// Folds the ranges of channel `ch` published by partners first, first + step, ...
+// (below parts, without q): `buf` holds the partners' words, D each.  The words of
+// N partners are loaded together, so they cost one round trip (28 slices of 8
+// workgroups in place, one at a time against eight 23.3 -> 22.6 us).  False, only in
+// the first exchange (gen 1), if one of those partners is closed.
+template <int N, int D>
+__device__ __forceinline__ bool fold_partners(uint64_t* buf, int ch, uint32_t first, uint32_t step, uint32_t parts,
+                                              uint32_t q, uint32_t gen, uint32_t polls, uint64_t* group, uint64_t* ex,
+                                              float& a, float& b) {
+  for (uint32_t limit = gen == 1u ? polls : kSpinLimit;; limit = kSpinLimit) {
+    uint32_t left = limit;  // no polls for the rest after the first that does not come
+    for (uint32_t r0 = first; r0 < parts; r0 += N * step) {
+      uint64_t v[N];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const uint32_t r = min(r0 + k * step, parts - 1);
-      v[k] = __hip_atomic_load(w + (size_t)r * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+      for (int k = 0; k < N; ++k)
+        v[k] = __hip_atomic_load(buf + (size_t)min(r0 + k * step, parts - 1) * D + ch, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const uint32_t r = r0 + k * step;
-      if (r >= parts || r == q) continue;
-      uint64_t x = v[k];
-      uint32_t spin = 0;
-      while ((uint32_t)(x >> 32) != gen && spin < kSpinLimit) {
-        __builtin_amdgcn_s_sleep(2);
-        x = __hip_atomic_load(w + (size_t)r * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ++spin;
+      for (int k = 0; k < N; ++k) {
+        const uint32_t r = r0 + k * step;
+        if (r >= parts || r == q) continue;
+        if (await_word(buf + (size_t)r * D + ch, v[k], gen, left))
+          fold_word(v[k], a, b);
+        else
+          left = 0;
       }
-      if ((uint32_t)(x >> 32) != gen) {
-        ++timeouts;
-        continue;
-      }
-      a = fminf(a, __uint_as_float((uint32_t)x << 16));
-      b = fmaxf(b, __uint_as_float((uint32_t)x & 0xFFFF0000u));
     }
+    if (left == limit && limit > 0u) return true;
+    if (limit == kSpinLimit) {  // counted; the codes are wrong
+      __hip_atomic_fetch_add(ex, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    }
+    bool closed = false;
+    for (uint32_t r = first; r < parts; r += step)
+      if (r != q) closed |= close_partner(group + 1 + r, ex);
+    if (closed) return false;  // (else every one of them is here: fold once more)
   }
 }
 
@@ -451,6 +489,51 @@ __device__ __forceinline__ bool roll_call_outcome(uint64_t* ex, uint32_t* shared
   return *shared == kAllHere;
 }
 
+// One slice by one workgroup: a range pass over its T rows, then the codes of its
+// image rows.  Taken where the partners of a group are not all here.  `red` (reset
+// to an empty range, and left so) and the scales are the workgroup's arrays.
+template <int D, int BITS, bool FAKE>
+__device__ __forceinline__ void slice_alone(const Params& p, uint32_t s, size_t slab, float (&red)[2 * D],
+                                            uint32_t (&g_meta)[D], float (&g_inv)[D]) {
+  constexpr int CPT = D / 8;
+  constexpr int LEVELS = (1 << BITS) - 1;
+  constexpr int ROW = D * BITS / 8;
+  int tid = threadIdx.x;
+  // What the resident path derives from its thread is not kept for this one (nor
+  // the shuffles' lanes: the range goes to LDS without them).
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, ch = 8 * (lane % CPT);
+  const uint16_t* slice = p.cache[0] + (size_t)s * p.T * D;
+  float mn[8], mx[8];
+  range_rows<D, kPartWaves, kSeqUnroll1, false>(slice, 0, p.T, mn, mx, tid);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    atomicMin(&red[ch + e], mn[e]);
+    atomicMax(&red[D + ch + e], mx[e]);
+  }
+  __syncthreads();
+  if (tid < D) {
+    const GroupScale gs = group_scale<LEVELS>(red[tid], red[D + tid]);
+    red[tid] = __builtin_inff();
+    red[D + tid] = -__builtin_inff();
+    g_meta[tid] = gs.meta;
+    g_inv[tid] = gs.inv;
+    if (!FAKE) __builtin_nontemporal_store(gs.meta, p.meta[0] + slab * D + tid);
+  }
+  __syncthreads();
+  GroupScale g[8];
+  float S[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    g[e].meta = g_meta[ch + e];
+    g[e].m = bf16_as_float(g[e].meta >> 16);
+    g[e].inv = g_inv[ch + e];
+    S[e] = bf16_as_float(g[e].meta & 0xFFFFu);
+  }
+  code_rows<D, BITS, FAKE, kPartWaves>(slice + (size_t)p.s0 * D, FAKE ? nullptr : p.codes[0] + slab * p.n * ROW,
+                                       FAKE ? p.out[0] + ((size_t)s * p.T + p.s0) * D : nullptr, 0, p.n, g, S, tid);
+}
+
 // FORM: the row slots (kPartRegSlots, kPartLdsSlots).
 // EX, how the partners' ranges are exchanged (an instantiation each, so the
 // common case keeps the smaller register footprint):
@@ -463,6 +546,8 @@ __device__ __forceinline__ bool roll_call_outcome(uint64_t* ex, uint32_t* shared
 //  rows, 2 bits: the split kernels' 1201 us -> 974 (18.6 us a round of two
 //  slices, 10 of them their rows at the chip's rate and 5.4 the two hops and
 //  the partners' skew); whole call 2020 -> 1890.
+// `expected`: the workgroups a spread launch's roll call waits for; otherwise the
+// polls before a partner is closed.
 template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_t parts, uint32_t rows_per_part,
@@ -478,6 +563,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   __shared__ float red[2 * D];               // per-channel min | max of the workgroup's rows
   __shared__ __attribute__((aligned(16))) uint32_t g_meta[D];
   __shared__ float g_inv[D];
+  __shared__ uint32_t incomplete;            // some partner of the group is not here
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -498,23 +584,37 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     red[tid] = __builtin_inff();
     red[D + tid] = -__builtin_inff();
   }
+  if (tid == 0) incomplete = 0;
   __syncthreads();
 
   uint32_t item = g;
   ResItem cur = res_item(p, item, n_items);
   if (!cur.valid) return;  // every partner of the group takes the same items
 
+  // The group's words behind the exchange area: a counter of slices, and a word per
+  // partner, where it enters itself (see close_partner) while its rows are loading.
+  uint64_t* const group = ex + kExHeader + (size_t)groups * 2u * parts * D + (size_t)g * (parts + 1u);
+  const bool enter = !SPREAD && parts > 1 && tid == kPartThreads - 1;
+  uint64_t entered = 0;
+  if (enter)
+    __hip_atomic_compare_exchange_strong(group + 1 + q, &entered, kHere, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+
   // First slice row of a slot for this lane (relative to t_lo): made opaque
   // once per slice so that the slots' row offsets are formed where they are
   // used (hoisted, they would all stay live and spill the resident rows).
   const int row0 = wave * RPW + rw;
   int rowb = row0;
-  auto slice_rsrc = [&](uint32_t s) { return make_rsrc(p.cache[0] + (size_t)s * T * D, (uint32_t)T * D * 2); };
-  auto src_off = [&](int slot) {
+  auto slice_rsrc = [&](uint32_t s) __attribute__((always_inline)) {
+    return make_rsrc(p.cache[0] + (size_t)s * T * D, (uint32_t)T * D * 2);
+  };
+  auto src_off = [&](int slot) __attribute__((always_inline)) {
     return (uint32_t)min(t_lo + slot * RS + rowb, t_hi - 1) * (D * 2) + (uint32_t)ch * 2;
   };
-  auto load_reg = [&](__amdgpu_buffer_rsrc_t r, int slot) { return buffer_load16(r, src_off(slot)); };
-  auto load_lds = [&](__amdgpu_buffer_rsrc_t r, int j) {
+  auto load_reg = [&](__amdgpu_buffer_rsrc_t r, int slot) __attribute__((always_inline)) {
+    return buffer_load16(r, src_off(slot));
+  };
+  auto load_lds = [&](__amdgpu_buffer_rsrc_t r, int j) __attribute__((always_inline)) {
     buffer_load16_lds(r, (lds_ptr)&rows_lds[j][wave * 64], src_off(j));
   };
 
@@ -524,7 +624,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   // finite BF16 high halves with any low bits order exactly as the BF16
   // values (ties only between equal high halves), so the minimum and maximum
   // words carry the exact BF16 extremes, recovered by masking once per slice.
-  auto range8 = [&](const u32x4 w) {
+  auto range8 = [&](const u32x4 w) __attribute__((always_inline)) {
     const float x[8] = {bf16_lo(w.x), __uint_as_float(w.x), bf16_lo(w.y), __uint_as_float(w.y),
                         bf16_lo(w.z), __uint_as_float(w.z), bf16_lo(w.w), __uint_as_float(w.w)};
 #pragma unroll
@@ -537,7 +637,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   // row t_hi - 1): the register slots (the compiler waits for their loads),
   // then, after every vector memory operation has completed (the scheduling
   // barrier keeps the LDS reads behind the wait), the LDS slots.
-  auto range_pass = [&]() {
+  auto range_pass = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       mn[e] = __builtin_inff();
@@ -547,8 +647,10 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     for (int k = 0; k < kRegSlots; ++k) range8(v[k]);
     __builtin_amdgcn_s_waitcnt(kWaitVmem0);
     __builtin_amdgcn_sched_barrier(0);
+    int at = tid;
+    if constexpr (kLdsSlots > 0) asm volatile("" : "+v"(at));  // (the slots' addresses as the rows' offsets)
 #pragma unroll
-    for (int j = 0; j < kLdsSlots; ++j) range8(rows_lds[j][tid]);
+    for (int j = 0; j < kLdsSlots; ++j) range8(rows_lds[j][at]);
   };
 
   {
@@ -566,6 +668,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     __shared__ uint32_t outcome;
     if (!roll_call_outcome(ex, &outcome)) return;
   }
+  if (enter && entered != 0) incomplete = 1;
 
   uint32_t seq = 0;
   for (;;) {
@@ -594,6 +697,8 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       }
     }
     __syncthreads();
+    const bool first = !SPREAD && seq == 0;
+    if (first && __builtin_amdgcn_readfirstlane(incomplete)) break;  // this partner was closed
     // 2. the slice's range from the partners' partial ranges, and its scales
     const size_t slab = (size_t)item;  // [slot][B] with slot = item / B
     if constexpr (WIDE) {
@@ -608,21 +713,17 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
                            __HIP_MEMORY_SCOPE_AGENT);
       const int chx = tid % D;
       float a = __builtin_inff(), b = -__builtin_inff();
-      uint32_t timeouts = 0;
       // (the longest form one word at a time: four in flight spill there, 52
       // bytes a lane instead of 12)
-      if constexpr (FORM == 0) {
-        for (uint32_t r = (uint32_t)tid / D; r < parts; r += kPartThreads / D)
-          if (r != q) fold_partner(buf + (size_t)r * D + chx, gen, a, b, timeouts);
-      } else {
-        fold_partners<4>(buf + chx, D, (uint32_t)tid / D, kPartThreads / D, parts, q, gen, a, b, timeouts);
-      }
-      if (timeouts) __hip_atomic_fetch_add(ex, (uint64_t)timeouts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!fold_partners<FORM == 0 ? 1 : 4, D>(buf, chx, (uint32_t)tid / D, kPartThreads / D, parts, q, gen, expected,
+                                               group, ex, a, b))
+        incomplete = 1;
       if (a <= b) {
         atomicMin(&red[chx], a);
         atomicMax(&red[D + chx], b);
       }
       __syncthreads();
+      if (first && __builtin_amdgcn_readfirstlane(incomplete)) break;
     }
     if constexpr (SPREAD) {
       const uint32_t gen = seq + 1;
@@ -633,11 +734,18 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         __hip_atomic_store(buf + (size_t)tid * parts + q, tagged_range(red[tid], red[D + tid], gen), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
       uint32_t timeouts = 0;
+      auto fold = [&](uint64_t* w, float& a, float& b) __attribute__((always_inline)) {
+        uint64_t x = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (await_word(w, x, gen, kSpinLimit))
+          fold_word(x, a, b);
+        else
+          ++timeouts;
+      };
       {
         const uint32_t sub = (uint32_t)wave % subs, chx = (uint32_t)wave / subs * parts + q;  // wave-uniform
         if (chx < (uint32_t)D) {
           float a = __builtin_inff(), b = -__builtin_inff();
-          fold_partner(buf + (size_t)chx * parts + sub * 64u + lane, gen, a, b, timeouts);
+          fold(buf + (size_t)chx * parts + sub * 64u + lane, a, b);
 #pragma unroll
           for (int off = 1; off < 64; off *= 2) {
             a = fminf(a, __shfl_xor(a, off));
@@ -650,7 +758,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       }
       if ((uint32_t)tid < subs * D) {
         float a = __builtin_inff(), b = -__builtin_inff();
-        fold_partner(folded + tid, gen, a, b, timeouts);
+        fold(folded + tid, a, b);
         if (a <= b) {
           atomicMin(&red[tid % D], a);
           atomicMax(&red[D + tid % D], b);
@@ -668,21 +776,16 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         uint64_t* buf = ex + kExHeader + ((size_t)g * 2u + (seq & 1u)) * parts * D;
         __hip_atomic_store(buf + (size_t)q * D + tid, tagged_range(a, b, gen), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t timeouts = 0;
-        if constexpr (FORM == 0) {
-          for (uint32_t r = 0; r < parts; ++r)
-            if (r != q) fold_partner(buf + (size_t)r * D + tid, gen, a, b, timeouts);
-        } else {
-          fold_partners<kSerialPartners>(buf + tid, D, 0, 1, parts, q, gen, a, b, timeouts);
-        }
-        if (timeouts) __hip_atomic_fetch_add(ex, (uint64_t)timeouts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!fold_partners<FORM == 0 ? 1 : kSerialPartners, D>(buf, tid, 0, 1, parts, q, gen, expected, group, ex, a, b))
+          incomplete = 1;
       }
       const GroupScale gs = group_scale<LEVELS>(a, b);
       g_meta[tid] = gs.meta;
       g_inv[tid] = gs.inv;
-      if (!FAKE && q == 0) __builtin_nontemporal_store(gs.meta, p.meta[0] + slab * D + tid);
     }
     __syncthreads();
+    if (EX == Exchange::kSerial && first && __builtin_amdgcn_readfirstlane(incomplete)) break;
+    if (!FAKE && q == 0 && tid < D) __builtin_nontemporal_store(g_meta[tid], p.meta[0] + slab * D + tid);
     ++seq;
     GroupScale gsc[8];  // .meta unused below; one-pass: .m read in emit
 #pragma unroll
@@ -703,7 +806,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     constexpr uint32_t kStride = FAKE ? D * 2 : ROW;
     const uint32_t lane_off = FAKE ? (uint32_t)ch * 2 : (uint32_t)c * BITS;
     const bool leader = (c & 3) == 0;
-    auto emit = [&](u32x4 w, int slot) {
+    auto emit = [&](u32x4 w, int slot) __attribute__((always_inline)) {
       asm volatile("" : "+v"(w));  // convert here, not reuse the range pass's values
       const int r = t_lo + slot * RS + rowb;
       const uint32_t off = r < t_hi ? (uint32_t)(r - p.s0) * kStride + lane_off : kDropped;
@@ -737,7 +840,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     // next slice's loads start at once.  The LDS slots are then all read
     // before any of them is refilled: an LDS read issued after a pending
     // direct-to-LDS load would wait for that load.
-    auto code_pass = [&](bool refill) {
+    auto code_pass = [&](bool refill) __attribute__((always_inline)) {
       const __amdgpu_buffer_rsrc_t r = slice_rsrc(nxt.s);
 #pragma unroll
       for (int k = 0; k < kRegSlots; ++k) {
@@ -745,9 +848,11 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         __builtin_amdgcn_sched_barrier(0);
         if (refill) v[k] = load_reg(r, kLdsSlots + k);
       }
+      int at = tid;
+      if constexpr (kLdsSlots > 0) asm volatile("" : "+v"(at));
 #pragma unroll
       for (int j = 0; j < kLdsSlots; ++j) {
-        emit(rows_lds[j][tid], j);
+        emit(rows_lds[j][at], j);
         __builtin_amdgcn_sched_barrier(0);
       }
       if (refill) {
@@ -759,12 +864,27 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     };
     if (!nxt.valid) {
       code_pass(false);
-      break;
+      return;
     }
     code_pass(true);
     range_pass();
     cur = nxt;
     item += groups;
+  }
+
+  // An incomplete group: slices from its counter.
+  __syncthreads();
+  if (tid < D) {
+    red[tid] = __builtin_inff();
+    red[D + tid] = -__builtin_inff();
+  }
+  for (;;) {
+    if (tid == 0)
+      incomplete = __hip_atomic_fetch_add((uint32_t*)group, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint32_t i = g + __builtin_amdgcn_readfirstlane(incomplete) * groups;
+    if (i >= n_items) return;
+    slice_alone<D, BITS, FAKE>(p, res_item(p, i, n_items).s, (size_t)i, red, g_meta, g_inv);
   }
 }
 
@@ -788,7 +908,7 @@ constexpr int kSplitWaves = kSplitThreads / 64;
 constexpr int kSplitRows = 2048;
 constexpr int kSplitRangeUnroll = 8;  // rows in flight per lane
 constexpr int kSplitCodeUnroll = 16;
-constexpr uint32_t kSplitBatch = 2 * kExMaxWgs;  // slices of 2D 32-bit words in the exchange area
+constexpr uint32_t kSplitBatch = 2 * kExAreaWgs;  // slices of 2D 32-bit words in the exchange area
 
 // Order-preserving unsigned image of a float (finite or infinite): a < b
 // implies ord(a) < ord(b), and every image is above 0.
@@ -919,7 +1039,7 @@ int kivi_partners(int T, int D) {
 // workgroups hold a slice, else (longer slices) the split kernels' range
 // words; a slice that one workgroup holds needs none.
 uint64_t kivi_workspace_bytes(int T, int D) {
-  return T > kivi_part_capacity(D) ? ((uint64_t)kExHeader + (uint64_t)kExMaxWgs * 2 * D) * 8 : 0;
+  return T > kivi_part_capacity(D) ? ((uint64_t)kExHeader + (uint64_t)kExAreaWgs * 2 * D) * 8 : 0;
 }
 
 // Compute units the persistent grids are sized for: the device's, or fewer
@@ -974,11 +1094,7 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   // longest 111.6, 4 of the middle one 113.2, 6 of the shortest 115.5; 3584
   // slices (3 bits) 1346, 1400 and 1501.  So more workgroups of a shorter form
   // than hold the slice are taken for one round only.
-  // Past kSerialPartners only as many as hold the slice: the dispatcher deals
-  // workgroups to the 8 XCDs in turn, so a group's partners follow each other
-  // on one XCD, and of up to four kernels on separate queues that share its 32
-  // compute units one has 8 or more workgroups there, a whole group, which
-  // then needs no other to finish.
+  // Past kSerialPartners only as many as hold the slice.
   const uint32_t wgs = (uint32_t)std::min(cus, kExMaxWgs);  // one workgroup per compute unit
   const uint32_t fewest = (uint32_t)kivi_partners(p.T, D);
   const uint32_t most = has_ws ? std::max(fewest, (uint32_t)kSerialPartners) : 1u;
@@ -1006,7 +1122,7 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
       pl->parts = (int)parts;
       pl->groups = groups;
       pl->rows_per_part = rows;
-      pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * 2 * parts * D) : 0;
+      pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * (2 * parts * D + parts + 1)) : 0;
     }
   }
   if (pl->resident) return hipSuccess;
@@ -1022,7 +1138,7 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   auto chip = [&](uint64_t active) { return 20u * active * (uint64_t)p.T / (per_slot * wgs); };
   best = chip(11ull * pl->n_items) / 5u + 500u;
   for (uint32_t parts = kSpreadMin; has_ws && parts <= kSpreadMax; parts *= 2) {
-    const uint32_t groups = std::min(pl->n_items, std::min(wgs, (uint32_t)kExMaxWgs / 2) / parts);  // fits the area
+    const uint32_t groups = std::min(pl->n_items, wgs / parts);
     const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
     if (groups == 0 || (uint64_t)p.T * D * 2 >= (1ull << 31)) continue;
     if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;  // every partner has a row
@@ -1051,18 +1167,27 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   return hipSuccess;
 }
 
-// Test hook: with HG_TEST_ABSENT=n in the environment a spread launch's roll
-// call waits for n workgroups that do not exist, so the split kernels do the work.
-static uint32_t absent_workgroups() {
-  const char* s = getenv("HG_TEST_ABSENT");
-  return s && *s ? (uint32_t)std::max(0, atoi(s)) : 0u;
+// Test hooks.  With HG_TEST_ABSENT=n in the environment a spread launch's roll
+// call waits for n workgroups that do not exist, so the split kernels do the
+// work, and the last eight groups of the other launches lack their last n
+// partners (at most all but one).  HG_TEST_POLLS: the polls before a partner is
+// closed (0: by the first that has to wait for it, while others still arrive).
+static uint32_t test_value(const char* name, uint32_t otherwise) {
+  const char* s = getenv(name);
+  return s && *s ? (uint32_t)std::max(0, atoi(s)) : otherwise;
 }
 
 template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 static void launch_part(const Params& p, const KiviPlan& pl, void* ws, dim3 grid, hipStream_t stream) {
+  uint32_t expected = grid.x;
+  if (EX == Exchange::kSpread) {
+    expected += test_value("HG_TEST_ABSENT", 0);
+  } else if (pl.parts > 1) {
+    expected = test_value("HG_TEST_POLLS", kGroupPolls);
+    grid.x -= std::min(8u * test_value("HG_TEST_ABSENT", 0), 8u * (uint32_t)(pl.parts - 1));
+  }
   hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, EX, FORM>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
-                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part,
-                     EX == Exchange::kSpread ? grid.x + absent_workgroups() : 0u, (uint64_t*)ws);
+                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part, expected, (uint64_t*)ws);
 }
 
 // The range and code launches of `nb` slices.

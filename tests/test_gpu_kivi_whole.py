@@ -288,6 +288,94 @@ def test_spread_groups_share_the_chip():
         assert all(torch.equal(pk[n], want[n]) for n in hg.BUFFERS)
 
 
+# Groups whose partners are not all on the chip: the ones that are close the
+# group and take its slices one workgroup a slice.  HG_TEST_ABSENT leaves the last
+# partners of the last eight groups out of the launch (several slices a group on
+# the small grids); the workspace's fourth word counts the partners closed.
+def _group_workload(D, T, H=11, B=2, bits=2):
+    w = small("kivi", D, bits, 1, img_len=T - 90, img_start=30, text=60, L=1, B=B, H=H,
+              n_protected=1).with_(kivi_group=0, name=f"kiviseq-groups-D{D}-T{T}")
+    K, V = synthkv.gen_kv(w)
+    K[0, :, :, T - 1, 5] = -4000.0  # extremes in the last and first rows
+    K[0, :, :, 0, 9] = 5000.0
+    return w, K, V, synthkv.protect_mask(w)
+
+
+ABSENT_CASES = [(128, "", 1600, "1"), (128, "32", 1700, "1"), (128, "32", 4000, "2"), (128, "", 3008, "7"),
+                (64, "16", 4000, "1"), (64, "128", 30000, "15"), (256, "", 1000, "3"), (256, "128", 7000, "1"),
+                (256, "", 20000, "31")]
+
+
+@pytest.mark.parametrize("D,cus,T,absent", ABSENT_CASES, ids=lambda v: str(v) or "all")
+def test_absent_partners(D, cus, T, absent, monkeypatch):
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    monkeypatch.setenv("HG_TEST_ABSENT", absent)
+    w, K, V, mask = _group_workload(D, T, bits=3 if D == 64 else 2)
+    ws = []
+
+    def prefill(pk):
+        _stale_words(pk["workspace"])
+        ws.append(pk["workspace"])
+    _assert_exact(compare_full(w, K, V, mask, prefill=prefill), w.name)
+    assert int(ws[0][24:32].view(torch.int64)[0]) > 0
+
+
+@pytest.mark.parametrize("D,cus,T,absent", ABSENT_CASES[:4] + ABSENT_CASES[7:], ids=lambda v: str(v) or "all")
+@pytest.mark.parametrize("inplace", [False, True])
+def test_absent_partners_fake(D, cus, T, absent, inplace, monkeypatch):
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    monkeypatch.setenv("HG_TEST_ABSENT", absent)
+    w, K, V, mask = _group_workload(D, T)
+    check_fake(w, K, V, mask, inplace, prefill_ws=_stale_words)
+
+
+@pytest.mark.parametrize("T,cus", [(1600, "32"), (3008, ""), (13000, ""), (40000, "")])
+def test_closing_beside_arrivals(T, cus, monkeypatch):
+    """Groups closed by the first partner that would have to wait, others still
+    arriving: whichever come first, in place and packed, the bytes are those of
+    a call alone."""
+    import paper_2609_35800_amd as hg
+    w, K, V, mask = _group_workload(128, T)
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    cfg = hg.make_config(**w.config_fields())
+    Kg, Vg = K.cuda(), V.cuda()
+    want, got = hg.alloc_packed(cfg, mask), hg.alloc_packed(cfg, mask)
+    ws = hg.alloc_fake_workspace(cfg, mask)
+    hg.hg_quantize(cfg, Kg, Vg, mask, want)
+    Kw, Vw = torch.clone(Kg), torch.clone(Vg)
+    hg.hg_fake_quantize(cfg, Kg, Vg, mask, Kw, Vw, ws)
+    monkeypatch.setenv("HG_TEST_POLLS", "0")
+    for _ in range(6):
+        hg.hg_quantize(cfg, Kg, Vg, mask, got)
+        assert all(torch.equal(got[n], want[n]) for n in hg.BUFFERS)
+        Ki, Vi = torch.clone(Kg), torch.clone(Vg)
+        hg.hg_fake_quantize(cfg, Ki, Vi, mask, Ki, Vi, ws)
+        assert torch.equal(Ki, Kw) and torch.equal(Vi, Vw)
+
+
+@pytest.mark.parametrize("T,H", [(3008, 29), (13000, 13), (40000, 9)])
+def test_groups_share_the_chip(T, H):
+    """Calls with groups of 8, 16 and 32 workgroups, each wanting every compute
+    unit, on four streams at once: the bytes are those of a call alone and no
+    wait runs out."""
+    import paper_2609_35800_amd as hg
+    w, K, V, mask = _group_workload(128, T, H=H, B=1)
+    cfg = hg.make_config(**w.config_fields())
+    Kg, Vg = K.cuda(), V.cuda()
+    want = hg.alloc_packed(cfg, mask)
+    hg.hg_quantize(cfg, Kg, Vg, mask, want)
+    packed = [hg.alloc_packed(cfg, mask) for _ in range(4)]
+    streams = [torch.cuda.Stream() for _ in packed]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for s, pk in zip(streams, packed):
+            hg.hg_quantize(cfg, Kg, Vg, mask, pk, stream=s)
+    torch.cuda.synchronize()
+    for pk in packed:
+        assert int(pk["workspace"][:8].view(torch.int64)[0]) == 0
+        assert all(torch.equal(pk[n], want[n]) for n in hg.BUFFERS)
+
+
 @pytest.mark.parametrize("which", ["none", "all", "last"])
 @pytest.mark.parametrize("keys_only", [0, 1])
 def test_degenerate_masks(which, keys_only):
