@@ -648,7 +648,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
     __builtin_amdgcn_s_waitcnt(kWaitVmem0);
     __builtin_amdgcn_sched_barrier(0);
     int at = tid;
-    if constexpr (kLdsSlots > 0) asm volatile("" : "+v"(at));  // (the slots' addresses as the rows' offsets)
+    if constexpr (kLdsSlots > 1) asm volatile("" : "+v"(at));  // (the slots' addresses as the rows' offsets)
 #pragma unroll
     for (int j = 0; j < kLdsSlots; ++j) range8(rows_lds[j][at]);
   };
@@ -849,7 +849,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         if (refill) v[k] = load_reg(r, kLdsSlots + k);
       }
       int at = tid;
-      if constexpr (kLdsSlots > 0) asm volatile("" : "+v"(at));
+      if constexpr (kLdsSlots > 1) asm volatile("" : "+v"(at));
 #pragma unroll
       for (int j = 0; j < kLdsSlots; ++j) {
         emit(rows_lds[j][at], j);
