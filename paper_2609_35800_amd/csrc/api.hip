@@ -340,7 +340,7 @@ static int run(bool quantize, const hg_config* cfg, const uint16_t* K, const uin
   // kernel's exchange words (one launch fewer)
   void* kivi_ws = z.workspace ? pk->workspace : nullptr;
   if (quantize && p.kivi_whole && kivi_ws) {
-    const hipError_t pe = hg::kivi_seq_clear_words(p, cfg->D, cfg->bits, false, kivi_ws, &p.clear_words);
+    const hipError_t pe = hg::kivi_seq_clear_words(p, cfg->D, kivi_ws, &p.clear_words);
     if (pe != hipSuccess) return fail(HG_ERR_HIP, "KIVI key kernel plan failed: %s", hipGetErrorString(pe));
     p.clear = (uint64_t*)kivi_ws;
   }
@@ -457,7 +457,7 @@ int fake_quantize(const hg_config* cfg, const uint16_t* K, const uint16_t* V, co
       e = step([&] { return hg::launch_retain_select(p, cfg->D, hg::RowCopy::kGather, stream); });
   }
   if (e == hipSuccess && p.kivi_whole && ws) {  // the one-pass kernel clears the key kernel's exchange words
-    e = hg::kivi_seq_clear_words(p, cfg->D, cfg->bits, true, ws, &p.clear_words);
+    e = hg::kivi_seq_clear_words(p, cfg->D, ws, &p.clear_words);
     p.clear = (uint64_t*)ws;
   }
   if (e == hipSuccess)

@@ -134,7 +134,7 @@ hipError_t launch_fake_quantize(const Params& p, int base, int D, int bits, bool
 // `cleared`: the words kivi_seq_clear_words gives were set to zero by an
 // earlier launch of the call (else the launch clears them itself).
 hipError_t launch_kivi_seq(const Params& p, int D, int bits, bool fake, void* ws, bool cleared, hipStream_t stream);
-hipError_t kivi_seq_clear_words(const Params& p, int D, int bits, bool fake, void* ws, uint32_t* words);
+hipError_t kivi_seq_clear_words(const Params& p, int D, void* ws, uint32_t* words);
 // Fewest workgroups of the resident kernel that hold a slice (0: the split
 // kernels), and
 // the exchange workspace bytes a call with T rows per slice needs (0: none).

@@ -1074,14 +1074,11 @@ struct KiviPlan {
   uint32_t clear_words = 0;
 };
 
-template <int D, int BITS, bool FAKE>
-static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
-  *pl = KiviPlan();
-  pl->n_items = (uint32_t)p.n_unprot_k * (uint32_t)p.B;
-  if (pl->n_items == 0) return hipSuccess;  // every key head kept in BF16: nothing to quantize here
-  int cus = 0;
-  hipError_t e = grid_cus(&cus);
-  if (e != hipSuccess) return e;
+// `T` rows and `n` image rows a slice, n_items slices, `cus` compute units.
+static KiviPlan plan_rows(int T, int n, int D, uint32_t n_items, bool has_ws, int cus) {
+  KiviPlan plan, *pl = &plan;
+  pl->n_items = n_items;
+  if (n_items == 0) return plan;  // every key head kept in BF16: nothing to quantize here
   // The resident kernel's workgroups per slice and form, by the time of the
   // call in twentieths of a slot's time with every compute unit loading: a
   // round (one slice per group) takes its rows at the chip's rate, or a
@@ -1096,15 +1093,15 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
   // than hold the slice are taken for one round only.
   // Past kSerialPartners only as many as hold the slice.
   const uint32_t wgs = (uint32_t)std::min(cus, kExMaxWgs);  // one workgroup per compute unit
-  const uint32_t fewest = (uint32_t)kivi_partners(p.T, D);
+  const uint32_t fewest = (uint32_t)kivi_partners(T, D);
   const uint32_t most = has_ws ? std::max(fewest, (uint32_t)kSerialPartners) : 1u;
   uint64_t best = ~0ull;
   for (int form = 0; form < kSpreadForm && fewest > 0; ++form) {
     for (uint32_t parts = fewest; parts <= most; ++parts) {
       const uint32_t cap = wgs / parts / 8u * 8u;  // groups held at once
-      const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
+      const uint32_t rows = ((uint32_t)T + parts - 1) / parts;
       if (cap == 0 || rows > (uint32_t)kivi_part_capacity(D, form)) continue;  // every row fits a slot
-      if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;             // every partner has a row
+      if ((uint64_t)(parts - 1) * rows >= (uint64_t)T) continue;             // every partner has a row
       const uint32_t groups = std::min((pl->n_items + 7u) / 8u * 8u, cap);
       const uint32_t rounds = (pl->n_items + groups - 1) / groups;
       if (form > 0 && rounds > 1 && parts > fewest) continue;
@@ -1112,7 +1109,7 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
       const uint32_t used = (rows + per_slot - 1) / per_slot;
       const uint32_t fixed = 7u * ((uint32_t)part_slots(form) - used) + 60u;
       auto round_cost = [&](uint64_t active) {  // groups with a slice in this round
-        return std::max<uint64_t>(11u * used, 20u * active * (uint64_t)p.T / ((uint64_t)per_slot * wgs)) + fixed;
+        return std::max<uint64_t>(11u * used, 20u * active * (uint64_t)T / ((uint64_t)per_slot * wgs)) + fixed;
       };
       const uint64_t cost = (rounds - 1) * round_cost(groups) + round_cost(pl->n_items - (rounds - 1) * groups);
       if (cost >= best) continue;
@@ -1125,46 +1122,80 @@ static hipError_t plan_k(const Params& p, bool has_ws, KiviPlan* pl) {
       pl->clear_words = parts > 1 ? (uint32_t)(kExHeader + (uint64_t)groups * (2 * parts * D + parts + 1)) : 0;
     }
   }
-  if (pl->resident) return hipSuccess;
-  // Slices past kMaxPartners workgroups: a spread group reads each slice once
-  // where the split kernels read it twice.  By the same count, a round's
-  // exchange takes 250 (two hops, and no loads in flight); the split kernels
-  // take 2.2 times the chip's time of every slice, and 500 for the second
-  // launch and the last chunks.  Split -> spread, whole calls (us, 2 bits,
-  // head_dim 128): slices of 131072 rows, 2 57.5 -> 51.3, 3 84 -> 85, 104 2072 ->
-  // 1879 (one-pass 3130 -> 2991); 17 of 100000 309 -> 293; one of 50000 33.9 ->
-  // 27.3; 7 of 300000 366 -> 334; 2 of 200000 71 -> 73.
+  if (pl->resident) return plan;
+  // Slices past kMaxPartners workgroups: a spread group reads each slice once where
+  // the split kernels read it twice.  Of the spread groups, the partners and form
+  // with the least by the count above, a round's exchange (two hops, and no loads in
+  // flight) taken as 250.  Spread groups or the split kernels by a count fitted to
+  // calls of 1 to 104 slices:
+  //  - a spread round takes its rows at the chip's rate, or a workgroup's own at 17
+  //    a slot if that is longer, 12 an empty slot and 75, with 256 partners 30 more
+  //    and at head_dim 256, whose words are twice as many, 75; the call 130 more, for
+  //    the empty launches behind it;
+  //  - each of the two split launches takes its chunks, a workgroup each, in waves of
+  //    one per compute unit: 31/40 of the chip's time of a full wave, and for the
+  //    rest of them 2/3 of that at least, a chunk's own time.
+  // Split -> spread, whole calls (us, 2 bits, the inputs in turn larger than the
+  // caches), in brackets where the split kernels are taken: head_dim 128, slices of
+  // 131072 rows, 1 46 -> 35, 2 58 -> 53, 3 [77 -> 77], 5 121 -> 106, 104 2072 ->
+  // 1879; of 80000 5 [73 -> 82], 8 116 -> 99; of 160000 3 [85 -> 90], 4 115 -> 98;
+  // head_dim 64, 5 of 100000 [53 -> 62]; head_dim 256, 17 of 25000 [136 -> 150], 1 of
+  // 100000 75 -> 46, 8 of 100000 [255 -> 263].
   const uint64_t per_slot = (uint64_t)(kPartWaves * (512 / D));
-  auto chip = [&](uint64_t active) { return 20u * active * (uint64_t)p.T / (per_slot * wgs); };
-  best = chip(11ull * pl->n_items) / 5u + 500u;
+  auto chip = [&](uint64_t active) { return 20u * active * (uint64_t)T / (per_slot * wgs); };
+  auto waves = [&](uint64_t rows) {
+    const uint64_t chunks = n_items * ((rows + kSplitRows - 1) / kSplitRows), rest = chunks % wgs;
+    const uint64_t wave = 20u * kSplitRows / per_slot;
+    return chunks / wgs * wave + (rest ? wave * 2 / 3 + wave * rest / (3 * wgs) : 0);
+  };
+  const uint64_t split_cost = (waves((uint64_t)T) + waves((uint64_t)n)) * 31 / 40;
+  KiviPlan spread;
+  uint64_t spread_cost = ~0ull;
+  best = ~0ull;
   for (uint32_t parts = kSpreadMin; has_ws && parts <= kSpreadMax; parts *= 2) {
-    const uint32_t groups = std::min(pl->n_items, wgs / parts);
-    const uint32_t rows = ((uint32_t)p.T + parts - 1) / parts;
-    if (groups == 0 || (uint64_t)p.T * D * 2 >= (1ull << 31)) continue;
-    if ((uint64_t)(parts - 1) * rows >= (uint64_t)p.T) continue;  // every partner has a row
-    const uint32_t rounds = (pl->n_items + groups - 1) / groups;
+    const uint32_t groups = std::min(n_items, wgs / parts);
+    const uint32_t rows = ((uint32_t)T + parts - 1) / parts;
+    if (groups == 0 || (uint64_t)T * D * 2 >= (1ull << 31)) continue;
+    if ((uint64_t)(parts - 1) * rows >= (uint64_t)T) continue;  // every partner has a row
+    const uint32_t rounds = (n_items + groups - 1) / groups;
     const uint32_t used = (uint32_t)((rows + per_slot - 1) / per_slot);
+    const uint32_t exchange = 75u + (parts == 256 ? 30u : 0u) + (D == 256 ? 75u : 0u);
+    const uint64_t last = n_items - (rounds - 1) * groups;  // groups with a slice in the last round
     for (int form : {2, kSpreadForm, 0}) {
       if (used > (uint32_t)part_slots(form)) continue;  // every row fits a slot
-      auto round_cost = [&](uint64_t active) {
-        return std::max<uint64_t>(11u * used, chip(active)) + 7u * ((uint32_t)part_slots(form) - used) + 250u;
+      const uint32_t empty = (uint32_t)part_slots(form) - used;
+      auto call = [&](uint32_t own, uint32_t fixed) {
+        return (rounds - 1) * (std::max<uint64_t>(own * used, chip(groups)) + fixed) +
+               std::max<uint64_t>(own * used, chip(last)) + fixed;
       };
-      const uint64_t cost = (rounds - 1) * round_cost(groups) + round_cost(pl->n_items - (rounds - 1) * groups) + 150u;
+      const uint64_t cost = call(11u, 7u * empty + 250u);
       if (cost >= best) continue;
       best = cost;
-      pl->resident = pl->spread = true;
-      pl->form = form;
-      pl->parts = (int)parts;
-      pl->groups = groups;
-      pl->rows_per_part = rows;
-      pl->clear_words = (uint32_t)(kExHeader + (uint64_t)groups * 2 * (parts + parts / 64) * D);
+      spread_cost = call(17u, 12u * empty + exchange) + 130u;
+      spread.form = form;
+      spread.parts = (int)parts;
+      spread.groups = groups;
+      spread.rows_per_part = rows;
+      spread.clear_words = (uint32_t)(kExHeader + (uint64_t)groups * 2 * (parts + parts / 64) * D);
     }
+  }
+  if (spread_cost < split_cost) {
+    plan = spread;
+    plan.n_items = n_items;
+    plan.resident = plan.spread = true;
   }
   if (has_ws) {
     pl->split = true;
-    pl->clear_words = std::max(pl->clear_words, (uint32_t)(kExHeader + (uint64_t)std::min(pl->n_items, kSplitBatch) * D));
+    pl->clear_words = std::max(pl->clear_words, (uint32_t)(kExHeader + (uint64_t)std::min(n_items, kSplitBatch) * D));
   }
-  return hipSuccess;
+  return plan;
+}
+
+static hipError_t plan_k(const Params& p, int D, bool has_ws, KiviPlan* pl) {
+  int cus = 0;
+  const hipError_t e = p.n_unprot_k > 0 ? grid_cus(&cus) : hipSuccess;
+  if (e == hipSuccess) *pl = plan_rows(p.T, p.n, D, (uint32_t)p.n_unprot_k * (uint32_t)p.B, has_ws, cus);
+  return e;
 }
 
 // Test hooks.  With HG_TEST_ABSENT=n in the environment a spread launch's roll
@@ -1204,7 +1235,7 @@ static void launch_split(const Params& p, uint32_t i0, uint32_t nb, uint32_t n_i
 template <int D, int BITS, bool FAKE>
 static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t stream) {
   KiviPlan pl;
-  hipError_t e = plan_k<D, BITS, FAKE>(p, ws != nullptr, &pl);
+  hipError_t e = plan_k(p, D, ws != nullptr, &pl);
   if (e != hipSuccess || pl.n_items == 0) return e;
   if (pl.clear_words > 0 && !cleared) {
     hipLaunchKernelGGL(zero_words_kernel, dim3(std::min<uint32_t>((pl.clear_words + 255) / 256, 1024)), dim3(256),
@@ -1266,47 +1297,45 @@ static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t 
   return hipGetLastError();
 }
 
-template <int D, int BITS, bool FAKE>
-static hipError_t plan_words(const Params& p, void* ws, uint32_t* clear_words) {
+template <int D, bool FAKE>
+static hipError_t kivi_d(const Params& p, int bits, void* ws, bool cleared, hipStream_t stream) {
+  switch (bits) {
+    case 2: return launch_k<D, 2, FAKE>(p, ws, cleared, stream);
+    case 3: return launch_k<D, 3, FAKE>(p, ws, cleared, stream);
+    case 4: return launch_k<D, 4, FAKE>(p, ws, cleared, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t kivi_seq_clear_words(const Params& p, int D, void* ws, uint32_t* words) {
   KiviPlan pl;
-  const hipError_t e = plan_k<D, BITS, FAKE>(p, ws != nullptr, &pl);
-  *clear_words = pl.clear_words;
+  const hipError_t e = plan_k(p, D, ws != nullptr, &pl);
+  *words = pl.clear_words;
   return e;
 }
 
-// With clear_words: only the number of workspace words the launch needs
-// cleared; else the launch.
-template <int D, bool FAKE>
-static hipError_t kivi_d(const Params& p, int bits, void* ws, bool cleared, uint32_t* clear_words,
-                         hipStream_t stream) {
-  switch (bits) {
-    case 2: return clear_words ? plan_words<D, 2, FAKE>(p, ws, clear_words) : launch_k<D, 2, FAKE>(p, ws, cleared, stream);
-    case 3: return clear_words ? plan_words<D, 3, FAKE>(p, ws, clear_words) : launch_k<D, 3, FAKE>(p, ws, cleared, stream);
-    case 4: return clear_words ? plan_words<D, 4, FAKE>(p, ws, clear_words) : launch_k<D, 4, FAKE>(p, ws, cleared, stream);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-static hipError_t kivi_dispatch(const Params& p, int D, int bits, bool fake, void* ws, bool cleared,
-                                uint32_t* clear_words, hipStream_t stream) {
-  switch (D) {
-    case 64: return fake ? kivi_d<64, true>(p, bits, ws, cleared, clear_words, stream)
-                         : kivi_d<64, false>(p, bits, ws, cleared, clear_words, stream);
-    case 128: return fake ? kivi_d<128, true>(p, bits, ws, cleared, clear_words, stream)
-                          : kivi_d<128, false>(p, bits, ws, cleared, clear_words, stream);
-    case 256: return fake ? kivi_d<256, true>(p, bits, ws, cleared, clear_words, stream)
-                          : kivi_d<256, false>(p, bits, ws, cleared, clear_words, stream);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-hipError_t kivi_seq_clear_words(const Params& p, int D, int bits, bool fake, void* ws, uint32_t* words) {
-  *words = 0;
-  return kivi_dispatch(p, D, bits, fake, ws, false, words, nullptr);
-}
-
 hipError_t launch_kivi_seq(const Params& p, int D, int bits, bool fake, void* ws, bool cleared, hipStream_t stream) {
-  return kivi_dispatch(p, D, bits, fake, ws, cleared, nullptr, stream);
+  switch (D) {
+    case 64: return fake ? kivi_d<64, true>(p, bits, ws, cleared, stream) : kivi_d<64, false>(p, bits, ws, cleared, stream);
+    case 128:
+      return fake ? kivi_d<128, true>(p, bits, ws, cleared, stream) : kivi_d<128, false>(p, bits, ws, cleared, stream);
+    case 256:
+      return fake ? kivi_d<256, true>(p, bits, ws, cleared, stream) : kivi_d<256, false>(p, bits, ws, cleared, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace hg
+
+// Host-only query for the tests of the plan above (not part of headguard.h): a
+// call's kernels on `cus` compute units with a workspace as hg_sizes reports it, as
+// {0 two-pass, 1 groups, 2 split kernels, 3 spread groups; partners; row slots;
+// groups; words of the workspace the launches use}.
+extern "C" void hg_test_kivi_plan(int T, int n, int D, uint32_t n_items, int cus, uint32_t out[5]) {
+  const hg::KiviPlan pl = hg::plan_rows(T, n, D, n_items, hg::kivi_workspace_bytes(T, D) > 0, cus);
+  out[0] = pl.spread ? 3u : pl.resident ? 1u : pl.split ? 2u : 0u;
+  out[1] = (uint32_t)pl.parts;
+  out[2] = pl.resident ? (uint32_t)hg::part_slots(pl.form) : 0u;
+  out[3] = pl.groups;
+  out[4] = pl.clear_words;
+}

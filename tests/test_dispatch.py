@@ -1,6 +1,7 @@
 """The rules that choose a call's kernels, queried on the host (no GPU): each
 choice is a launch the runtime accepts and the kernel's on-chip memory holds."""
 import ctypes as C
+import random
 
 import pytest
 
@@ -24,3 +25,52 @@ def test_selection_with_the_values_stays_under_the_launch_limit(n, D):
     most = (2**32 - 1) // THREADS // per_slice
     assert select_with_values(most, n, D, 2) and not select_with_values(most + 1, n, D, 2)
     assert not select_with_values(2**23, n, D, 2) or 2**23 * per_slice * THREADS < 2**32
+
+
+SPLIT, GROUPS, SPREAD = 2, 1, 3
+
+
+def kivi_plan(T, D, items, n=None, cus=256):
+    """(kind, partners, row slots, groups, workspace words) of a call with
+    whole-sequence keys."""
+    out = (C.c_uint32 * 5)()
+    f = hg.library().hg_test_kivi_plan
+    f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_uint32 * 5], None
+    f(T, T - 800 if n is None else n, D, items, cus, out)
+    return tuple(out)
+
+
+# Slices past 32 workgroups' rows: spread groups or the split kernels, whichever was
+# measured faster (D, rows, slices), 2 and 4 bits, quantize and one-pass.
+@pytest.mark.parametrize("D,T,items", [(128, 98304, 5), (128, 100000, 5), (128, 160000, 3), (128, 200000, 5),
+                                       (64, 100000, 3), (64, 100000, 5), (64, 400000, 5),
+                                       (64, 400000, 17), (256, 25000, 17), (256, 100000, 4), (256, 100000, 5),
+                                       (256, 100000, 8), (256, 100000, 17)])
+def test_split_kernels_where_spread_groups_are_slower(D, T, items):
+    assert kivi_plan(T, D, items)[0] == SPLIT
+
+
+@pytest.mark.parametrize("D,T,items", [(128, 50000, 1), (128, 50000, 4), (128, 80000, 8), (128, 98304, 6),
+                                       (128, 131072, 1), (128, 131072, 2), (128, 131072, 5), (128, 131072, 104),
+                                       (128, 300000, 2), (64, 131072, 8), (64, 131072, 104), (64, 600000, 1),
+                                       (256, 25000, 1), (256, 25000, 8), (256, 32768, 17), (256, 65536, 1),
+                                       (256, 100000, 1), (256, 150000, 4)])
+def test_spread_groups_where_they_are_faster(D, T, items):
+    assert kivi_plan(T, D, items)[0] == SPREAD
+
+
+def test_every_plan_fits_the_workspace():
+    """The words a plan's launches use lie in the workspace hg_packed_sizes reports,
+    and every row of a slice has a slot."""
+    rng = random.Random(7)
+    for _ in range(4000):
+        D = rng.choice([64, 128, 256])
+        T = int(2 ** rng.uniform(0, 21))
+        L, B, H = rng.randint(1, 80), rng.randint(1, 64), rng.randint(1, 32)
+        cfg = hg.make_config(L=L, B=B, H=H, T=T, D=D, img_start=0, img_len=T, bits=2, base="kivi", keys_only=1,
+                             kivi_group=0)
+        have = hg.hg_packed_sizes(cfg, [0] * (L * H))["workspace"]
+        kind, parts, slots, groups, words = kivi_plan(T, D, L * B * H, T, rng.choice([1, 8, 31, 64, 256, 304, 1024]))
+        assert words * 8 <= have
+        if kind in (GROUPS, SPREAD):
+            assert -(-T // parts) <= slots * 8192 // D and (parts == 1 or have > 0)

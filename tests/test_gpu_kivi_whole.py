@@ -224,7 +224,8 @@ def _spread_cases():
     out = []
     for D in (64, 128, 256):
         r = 8192 // D
-        out += [(D, "", 32 * 24 * r + 1, 4), (D, "", 64 * 16 * r, 4), (D, "128", 64 * 16 * r + 1, 4),
+        few = 9 if D == 64 else 4  # (few slices at head_dim 64 go to the split kernels)
+        out += [(D, "", 32 * 24 * r + 1, few), (D, "", 64 * 16 * r, few), (D, "128", 64 * 16 * r + 1, 5),
                 (D, "64", 64 * 24 * r, 4), (D, "", 64 * 24 * r + 1, 4), (D, "", 128 * 8 * r + 1, 1)]
     out += [(256, "128", 128 * 16 * 32, 4), (256, "", 128 * 16 * 32 + 1, 4), (256, "", 256 * 8 * 32, 1),
             (256, "", 256 * 24 * 32, 1), (256, "", 256 * 24 * 32 + 1, 1)]
