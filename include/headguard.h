@@ -78,14 +78,15 @@
  * another (a bounded number of polls).  They first agree that all of them are
  * on the chip, which kernels on other streams can prevent: the partners of a
  * slice that find some missing for about half a millisecond take it one
- * workgroup a slice, and past 32 workgroups' rows the whole call goes to the
- * kernels for slices past 256 workgroups' rows, where chunks of each slice
- * merge their ranges into the same workspace with atomics and a second launch
- * writes the codes.  So calls on several streams, or beside other kernels, delay
- * one another but do not change the results.  (A wait after that agreement
- * could only run out if the device stopped running a resident workgroup for
- * about a second; the workspace's first word counts such waits, after which the
- * codes of the slices affected are wrong.)
+ * workgroup a slice, and past 32 workgroups' rows the whole call goes, after
+ * about its own time and at most 0.13 ms, to the kernels for slices past 256
+ * workgroups' rows, where chunks of each slice merge their ranges into the same
+ * workspace with atomics and a second launch writes the codes.  So calls on
+ * several streams, or beside other kernels, delay one another but do not change
+ * the results.  (A wait after that agreement could only run out if the device
+ * stopped running a resident workgroup for about a second; the workspace's first
+ * word counts such waits, after which the codes of the slices affected are
+ * wrong.)
  *
  * Every buffer a call writes must be disjoint from every other buffer of the
  * call (HG_ERR_POINTER, checked on the host from the pointers and the sizes

@@ -269,8 +269,12 @@ enum : uint64_t { kUndecided = 0, kAllHere = 1, kNotAll = 2 };
 // long enough to wait for a short kernel of another stream, whose compute units
 // the missing partners then take.
 constexpr uint32_t kGroupPolls = 512;
-// Polls of the roll call's outcome (about 1 us each) before a workgroup closes it.
-constexpr uint32_t kRollCallPolls = 128;
+// Polls of the roll call's outcome (about 1 us each) before a workgroup closes it:
+// at most these, and about the time the call's key launches take if that is less, so
+// that on a chip with other kernels, where the split kernels then do the work, a call
+// takes at most about twice its time; and enough for the workgroups of one launch,
+// which arrive within a few us of each other.
+constexpr uint32_t kRollCallPolls = 128, kRollCallPollsMin = 24;
 enum class Exchange { kSerial, kWide, kSpread };
 
 typedef __attribute__((address_space(3))) void* lds_ptr;
@@ -459,7 +463,7 @@ __device__ __forceinline__ bool fold_partners(uint64_t* buf, int ch, uint32_t fi
 // The roll call of a spread launch.  A spread group can only exchange when
 // every workgroup of the grid is on the chip, which another stream's kernel may
 // prevent, so the grid agrees first: the last of `expected` arrivals opens the
-// exchange, and a workgroup that has polled the outcome kRollCallPolls times
+// exchange, and a workgroup that has polled the outcome `polls` times
 // closes it.  One compare-and-swap decides, and nothing was published or stored
 // before it: after kNotAll every workgroup ends and the split kernels, launched
 // behind in either case, do the call's work instead.  All threads of the
@@ -472,10 +476,10 @@ __device__ __forceinline__ void roll_call_arrive(uint64_t* ex, uint32_t expected
                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-__device__ __forceinline__ bool roll_call_outcome(uint64_t* ex, uint32_t* shared) {
+__device__ __forceinline__ bool roll_call_outcome(uint64_t* ex, uint32_t polls, uint32_t* shared) {
   if (threadIdx.x == 0) {
     uint64_t seen = kUndecided;
-    for (uint32_t poll = 0; poll < kRollCallPolls && seen == kUndecided; ++poll) {
+    for (uint32_t poll = 0; poll < polls && seen == kUndecided; ++poll) {
       if (poll) __builtin_amdgcn_s_sleep(8);
       seen = __hip_atomic_load(ex + kExOutcome, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -546,12 +550,12 @@ __device__ __forceinline__ void slice_alone(const Params& p, uint32_t s, size_t 
 //  rows, 2 bits: the split kernels' 1201 us -> 974 (18.6 us a round of two
 //  slices, 10 of them their rows at the chip's rate and 5.4 the two hops and
 //  the partners' skew); whole call 2020 -> 1890.
-// `expected`: the workgroups a spread launch's roll call waits for; otherwise the
-// polls before a partner is closed.
+// `expected`: the workgroups a spread launch's roll call waits for; `polls`: the
+// polls before it, or a partner, is closed.
 template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_t parts, uint32_t rows_per_part,
-                      uint32_t expected, uint64_t* __restrict__ ex) {
+                      uint32_t expected, uint32_t polls, uint64_t* __restrict__ ex) {
   constexpr bool WIDE = EX == Exchange::kWide, SPREAD = EX == Exchange::kSpread;
   constexpr int LEVELS = (1 << BITS) - 1;
   constexpr int ROW = D * BITS / 8;
@@ -666,7 +670,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
   range_pass();  // every load is complete, also for a workgroup that now ends
   if constexpr (SPREAD) {
     __shared__ uint32_t outcome;
-    if (!roll_call_outcome(ex, &outcome)) return;
+    if (!roll_call_outcome(ex, polls, &outcome)) return;
   }
   if (enter && entered != 0) incomplete = 1;
 
@@ -715,7 +719,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
       float a = __builtin_inff(), b = -__builtin_inff();
       // (the longest form one word at a time: four in flight spill there, 52
       // bytes a lane instead of 12)
-      if (!fold_partners<FORM == 0 ? 1 : 4, D>(buf, chx, (uint32_t)tid / D, kPartThreads / D, parts, q, gen, expected,
+      if (!fold_partners<FORM == 0 ? 1 : 4, D>(buf, chx, (uint32_t)tid / D, kPartThreads / D, parts, q, gen, polls,
                                                group, ex, a, b))
         incomplete = 1;
       if (a <= b) {
@@ -776,7 +780,7 @@ void kivi_part_kernel(const Params p, uint32_t n_items, uint32_t groups, uint32_
         uint64_t* buf = ex + kExHeader + ((size_t)g * 2u + (seq & 1u)) * parts * D;
         __hip_atomic_store(buf + (size_t)q * D + tid, tagged_range(a, b, gen), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
-        if (!fold_partners<FORM == 0 ? 1 : kSerialPartners, D>(buf, tid, 0, 1, parts, q, gen, expected, group, ex, a, b))
+        if (!fold_partners<FORM == 0 ? 1 : kSerialPartners, D>(buf, tid, 0, 1, parts, q, gen, polls, group, ex, a, b))
           incomplete = 1;
       }
       const GroupScale gs = group_scale<LEVELS>(a, b);
@@ -1070,7 +1074,7 @@ struct KiviPlan {
   bool spread = false;
   int parts = 0;
   int form = 0;
-  uint32_t n_items = 0, groups = 0, rows_per_part = 0;
+  uint32_t n_items = 0, groups = 0, rows_per_part = 0, polls = kGroupPolls;
   uint32_t clear_words = 0;
 };
 
@@ -1183,6 +1187,8 @@ static KiviPlan plan_rows(int T, int n, int D, uint32_t n_items, bool has_ws, in
     plan = spread;
     plan.n_items = n_items;
     plan.resident = plan.spread = true;
+    // (a unit of the count is about 0.038 us)
+    plan.polls = (uint32_t)std::min<uint64_t>(kRollCallPolls, std::max<uint64_t>(kRollCallPollsMin, spread_cost / 26));
   }
   if (has_ws) {
     pl->split = true;
@@ -1210,15 +1216,15 @@ static uint32_t test_value(const char* name, uint32_t otherwise) {
 
 template <int D, int BITS, bool FAKE, Exchange EX, int FORM>
 static void launch_part(const Params& p, const KiviPlan& pl, void* ws, dim3 grid, hipStream_t stream) {
-  uint32_t expected = grid.x;
+  uint32_t expected = grid.x, polls = pl.polls;
   if (EX == Exchange::kSpread) {
     expected += test_value("HG_TEST_ABSENT", 0);
   } else if (pl.parts > 1) {
-    expected = test_value("HG_TEST_POLLS", kGroupPolls);
+    polls = test_value("HG_TEST_POLLS", polls);
     grid.x -= std::min(8u * test_value("HG_TEST_ABSENT", 0), 8u * (uint32_t)(pl.parts - 1));
   }
   hipLaunchKernelGGL((kivi_part_kernel<D, BITS, FAKE, EX, FORM>), grid, dim3(kPartThreads), 0, stream, p, pl.n_items,
-                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part, expected, (uint64_t*)ws);
+                     pl.groups, (uint32_t)pl.parts, pl.rows_per_part, expected, polls, (uint64_t*)ws);
 }
 
 // The range and code launches of `nb` slices.
@@ -1330,12 +1336,14 @@ hipError_t launch_kivi_seq(const Params& p, int D, int bits, bool fake, void* ws
 // Host-only query for the tests of the plan above (not part of headguard.h): a
 // call's kernels on `cus` compute units with a workspace as hg_sizes reports it, as
 // {0 two-pass, 1 groups, 2 split kernels, 3 spread groups; partners; row slots;
-// groups; words of the workspace the launches use}.
-extern "C" void hg_test_kivi_plan(int T, int n, int D, uint32_t n_items, int cus, uint32_t out[5]) {
+// groups; words of the workspace the launches use; polls before a missing workgroup
+// is given up}.
+extern "C" void hg_test_kivi_plan(int T, int n, int D, uint32_t n_items, int cus, uint32_t out[6]) {
   const hg::KiviPlan pl = hg::plan_rows(T, n, D, n_items, hg::kivi_workspace_bytes(T, D) > 0, cus);
   out[0] = pl.spread ? 3u : pl.resident ? 1u : pl.split ? 2u : 0u;
   out[1] = (uint32_t)pl.parts;
   out[2] = pl.resident ? (uint32_t)hg::part_slots(pl.form) : 0u;
   out[3] = pl.groups;
   out[4] = pl.clear_words;
+  out[5] = pl.polls;
 }

@@ -31,11 +31,11 @@ SPLIT, GROUPS, SPREAD = 2, 1, 3
 
 
 def kivi_plan(T, D, items, n=None, cus=256):
-    """(kind, partners, row slots, groups, workspace words) of a call with
+    """(kind, partners, row slots, groups, workspace words, polls) of a call with
     whole-sequence keys."""
-    out = (C.c_uint32 * 5)()
+    out = (C.c_uint32 * 6)()
     f = hg.library().hg_test_kivi_plan
-    f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_uint32 * 5], None
+    f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_uint32 * 6], None
     f(T, T - 800 if n is None else n, D, items, cus, out)
     return tuple(out)
 
@@ -70,7 +70,14 @@ def test_every_plan_fits_the_workspace():
         cfg = hg.make_config(L=L, B=B, H=H, T=T, D=D, img_start=0, img_len=T, bits=2, base="kivi", keys_only=1,
                              kivi_group=0)
         have = hg.hg_packed_sizes(cfg, [0] * (L * H))["workspace"]
-        kind, parts, slots, groups, words = kivi_plan(T, D, L * B * H, T, rng.choice([1, 8, 31, 64, 256, 304, 1024]))
+        kind, parts, slots, groups, words, _ = kivi_plan(T, D, L * B * H, T, rng.choice([1, 8, 31, 64, 256, 304, 1024]))
         assert words * 8 <= have
         if kind in (GROUPS, SPREAD):
             assert -(-T // parts) <= slots * 8192 // D and (parts == 1 or have > 0)
+
+
+@pytest.mark.parametrize("T,items,us", [(50000, 1, 24), (131072, 1, 33), (131072, 2, 48), (131072, 104, 1750)])
+def test_a_busy_chip_delays_a_spread_call_by_its_own_time_at_most(T, items, us):
+    """A poll takes about 1 us; `us`: the whole call measured alone."""
+    kind, polls = kivi_plan(T, 128, items)[0::5]
+    assert kind == SPREAD and 16 <= polls <= min(128, us)
