@@ -275,25 +275,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
 }
 
 // Token retention: the value tiles and the selection, which needs only the key
-// norms of the launch before.  The first workgroup of each slice's run selects
-// its retained tokens, the others quantize its value tiles, so the selection,
-// a chain of barriers and LDS passes with little traffic, runs among streaming
-// workgroups.  A launch for both and one for the selection -> keys, then values
+// norms of the launch before.  One workgroup of each slice's run selects its
+// retained tokens, the others quantize its value tiles, so the selection, a chain
+// of barriers and LDS passes with little traffic, runs among streaming
+// workgroups.  Workgroups are dealt in turn to the 8 XCDs and to their compute
+// units, so the selecting one has a place of its own in each run: always the first,
+// the selections fall to a few compute units where the run's length has a divisor
+// in common with those, and the rest wait for these (head_dim 64, 4 bits, 1296
+// // tokens, 900 MB, 2 % retained: a launch for the selection 266 us, first of the run
+// 307, placed 260; 10 % retained 283, 332, 277).  A launch for both and one for the selection -> keys, then values
 // and selection (us, 8 heads, 3456 tokens, 2 bits): one layer 22.9 -> 17.9, 4
 // prompts 34.8 -> 27.2, 64 prompts 218 -> 210, 256 prompts (two launches and one)
 // 811 -> 800; head_dim 256, 64 prompts 434 -> 430.
+__host__ __device__ inline uint32_t select_place(uint32_t s, uint32_t run) { return (s * 0x9E3779B1u >> 16) % run; }
+
 template <int D, int BITS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWaves)))
 void quantize_values_select_kernel(const Params p) {
   extern __shared__ uint32_t lds_keys[];  // n keys
   const uint32_t run = (uint32_t)p.tiles + 1u;
-  const uint32_t s = blockIdx.x / run, i = blockIdx.x % run;
-  if (i == 0) {
+  const uint32_t s = blockIdx.x / run, i = blockIdx.x % run, at = select_place(s, run);
+  if (i == at) {
     retain_select<true, D, RowCopy::kGather>(p, s, lds_keys);
     return;
   }
   const SliceRoute r = route_slice(p, 1, s);
-  quantize_tile<HG_BASE_MINMAX, D, BITS, false>(p, Slice{1, (int)i - 1, s, r.b, r.kept, r.slot});
+  quantize_tile<HG_BASE_MINMAX, D, BITS, false>(p, Slice{1, (int)(i < at ? i : i - 1u), s, r.b, r.kept, r.slot});
 }
 
 // Wavefronts per SIMD of a quantize launch (each measured against 6 on the
@@ -455,7 +462,8 @@ hipError_t launch_quantize(const Params& p, int base, int D, int bits, bool norm
 
 }  // namespace hg
 
-// Host-only query for the tests of the rule above (not part of headguard.h).
+// Host-only queries for the tests of the rules above (not part of headguard.h).
+extern "C" uint32_t hg_test_select_place(uint32_t s, uint32_t run) { return hg::select_place(s, run); }
 extern "C" int hg_test_select_with_values(uint64_t slices, uint64_t n, int D, int bits) {
   return hg::select_fits(slices, n, D, bits);
 }

@@ -27,6 +27,23 @@ def test_selection_with_the_values_stays_under_the_launch_limit(n, D):
     assert not select_with_values(2**23, n, D, 2) or 2**23 * per_slice * THREADS < 2**32
 
 
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6, 7, 10, 11, 20, 21, 26, 31, 54, 55, 63])
+def test_selections_are_spread_over_the_chip(tiles):
+    """Consecutive workgroups go to the 8 XCDs in turn, and those of an XCD to its 32
+    compute units: with a slice's selecting workgroup and its `tiles` value tiles in
+    one run, no XCD gets more than 1.25 and no compute unit more than 2 times its
+    share of the selections (always first, a run of 8 would put all on one XCD)."""
+    f = hg.library().hg_test_select_place
+    f.argtypes, f.restype = [C.c_uint32, C.c_uint32], C.c_uint32
+    run, xcd, cu, slices = tiles + 1, [0] * 8, [0] * 256, 16384
+    for s in range(slices):
+        at = f(s, run)
+        assert at < run
+        xcd[(s * run + at) % 8] += 1
+        cu[(s * run + at) % 256] += 1
+    assert max(xcd) <= 1.25 * slices / 8 and max(cu) <= 2 * slices / 256
+
+
 SPLIT, GROUPS, SPREAD = 2, 1, 3
 
 
