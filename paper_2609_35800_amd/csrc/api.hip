@@ -507,3 +507,8 @@ int hg_dequantize(const hg_config* cfg, const uint8_t* mask, const hg_packed* in
 }
 
 }  // extern "C"
+
+// Host-only query for the tests of the rule (not part of headguard.h).
+extern "C" int hg_test_retain_in_dequantize(uint64_t bytes, int64_t n, int64_t k, int D) {
+  return hg::retain_in_dequantize(bytes, n, k, D);
+}

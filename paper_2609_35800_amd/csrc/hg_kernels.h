@@ -158,10 +158,22 @@ hipError_t launch_retain_rows(const Params& p, int D, RowCopy mode, hipStream_t 
 // prompts 16.1 -> 13.5 (16.6 -> 13.2), 16 prompts 47.1 -> 43.5 (49.3 -> 46.1), 64
 // prompts 170 -> 168 (213 -> 208); 256 prompts, two launches, 776 -> 857 (825 ->
 // 845), their wavefronts waiting for the list, 773 (809) without occupancy caps.
+// Rows left out of a tile and stored later are writes of their own, which shows
+// once what a call reads outgrows the caches: at head_dim 64 (rows of 128 bytes)
+// from a half of a GiB, at 128 from three quarters where more than one token in 32
+// is retained, at 256 not below 1 GiB.  Past those the rows are written back
+// (launch -> in the kernel, us, 2 bits; inputs in the caches as far as they fit:
+// head_dim 128, 1296 tokens, 6 % retained, 759 MB 163 -> 150, 950 MB 234 -> 261; 2 %,
+// 950 MB 201 -> 193; head_dim 64, 5000 tokens, 5 %, 983 MB 245 -> 274; 256, 1280
+// tokens, 6 %, 849 MB 196 -> 170; from memory: head_dim 64, 1296 tokens, 2 %, 600 MB
+// 3.5 % more).
 constexpr int kFusedRetained = 256;
-inline bool retain_in_dequantize(const Params& p, int D) {
-  return p.k > 0 && p.k <= kFusedRetained && image_bytes(p, D) < kOneLaunchBytes;
+inline bool retain_in_dequantize(uint64_t bytes, int64_t n, int64_t k, int D) {
+  const uint64_t quarter = kOneLaunchBytes / 4;
+  const uint64_t limit = D == 64 ? 2 * quarter : D == 128 && 32 * k > n ? 3 * quarter : kOneLaunchBytes;
+  return k > 0 && k <= kFusedRetained && bytes < limit;
 }
+inline bool retain_in_dequantize(const Params& p, int D) { return retain_in_dequantize(image_bytes(p, D), p.n, p.k, D); }
 
 // Host side: the one-pass call (api.hip) with its token-retention workspace
 // supplied by `get_ws(need, &ws)` after the host-side argument checks, only

@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kMinWa
 // units, so the selecting one has a place of its own in each run: always the first,
 // the selections fall to a few compute units where the run's length has a divisor
 // in common with those, and the rest wait for these (head_dim 64, 4 bits, 1296
-// // tokens, 900 MB, 2 % retained: a launch for the selection 266 us, first of the run
+// tokens, 900 MB, 2 % retained: a launch for the selection 266 us, first of the run
 // 307, placed 260; 10 % retained 283, 332, 277).  A launch for both and one for the selection -> keys, then values
 // and selection (us, 8 heads, 3456 tokens, 2 bits): one layer 22.9 -> 17.9, 4
 // prompts 34.8 -> 27.2, 64 prompts 218 -> 210, 256 prompts (two launches and one)

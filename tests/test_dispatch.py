@@ -44,6 +44,19 @@ def test_selections_are_spread_over_the_chip(tiles):
     assert max(xcd) <= 1.25 * slices / 8 and max(cu) <= 2 * slices / 256
 
 
+# Dequantize with retention: (head_dim, tokens, retained, slices) where the rows were
+# measured to be stored faster in the dequantize kernel, or by a launch of their own.
+@pytest.mark.parametrize("D,n,k,slices,fused", [
+    (128, 3328, 67, 8, True), (128, 1296, 78, 1144, True), (128, 1296, 26, 1432, True), (128, 3328, 50, 568, True),
+    (128, 1296, 78, 1432, False), (128, 1296, 130, 1432, False), (128, 5000, 250, 384, False),
+    (64, 1296, 26, 1720, False), (64, 1296, 26, 1144, True), (64, 5000, 250, 768, False), (64, 640, 38, 5544, False),
+    (256, 1280, 77, 648, True), (256, 1296, 130, 640, True), (128, 1000, 257, 8, False), (128, 3328, 67, 2048, False)])
+def test_retained_rows_in_the_dequantize_kernel(D, n, k, slices, fused):
+    f = hg.library().hg_test_retain_in_dequantize
+    f.argtypes, f.restype = [C.c_uint64, C.c_int64, C.c_int64, C.c_int], C.c_int
+    assert bool(f(4 * slices * n * D, n, k, D)) == fused
+
+
 SPLIT, GROUPS, SPREAD = 2, 1, 3
 
 
