@@ -1263,8 +1263,8 @@ static hipError_t launch_k(const Params& p, void* ws, bool cleared, hipStream_t 
       wide ? launch_part<D, BITS, FAKE, Exchange::kWide, 1>(p, pl, ws, grid, stream)
            : launch_part<D, BITS, FAKE, Exchange::kSerial, 1>(p, pl, ws, grid, stream);
     else
-      wide ? launch_part<D, BITS, FAKE, Exchange::kWide, 2>(p, pl, ws, grid, stream)
-           : launch_part<D, BITS, FAKE, Exchange::kSerial, 2>(p, pl, ws, grid, stream);
+      // (more than kSerialPartners hold at least 12 slots of rows each)
+      launch_part<D, BITS, FAKE, Exchange::kSerial, 2>(p, pl, ws, grid, stream);
     e = hipGetLastError();
     if (e != hipSuccess || !pl.spread) return e;
   }

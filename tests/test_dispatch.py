@@ -111,3 +111,13 @@ def test_a_busy_chip_delays_a_spread_call_by_its_own_time_at_most(T, items, us):
     """A poll takes about 1 us; `us`: the whole call measured alone."""
     kind, polls = kivi_plan(T, 128, items)[0::5]
     assert kind == SPREAD and 16 <= polls <= min(128, us)
+
+
+@pytest.mark.parametrize("D", [64, 128, 256])
+def test_the_shortest_form_has_no_wide_groups(D):
+    """Groups of more than 8 partners, which exchange in another way, never have the
+    form of 8 row slots: it is not built for them."""
+    for T in range(8192 // D, 32 * 24 * 8192 // D + 2, 97):
+        for items in (1, 9, 60, 1000):
+            kind, parts, slots = kivi_plan(T, D, items)[:3]
+            assert kind != GROUPS or parts <= 8 or slots > 8
