@@ -341,8 +341,8 @@ static size_t values_select_lds(int bits) {
   return bits == 2 ? kValuesSelectLds<D, 2> : bits == 3 ? kValuesSelectLds<D, 3> : kValuesSelectLds<D, 4>;
 }
 
-// Spans whose norms fit that LDS (6000 tokens at 2 bits and head_dim 128; 3900
-// at head_dim 256): a larger reservation would cost the value tiles their
+// Spans whose norms fit that LDS (5711 tokens at 2 bits, 6686 at 3, 8052 at
+// 4; 3956 at head_dim 256): a larger reservation would cost the value tiles their
 // occupancy, so longer spans select in a launch of their own.  So do slices so
 // many and short that the launch, one workgroup a slice longer than that of the
 // values alone, would have 2^32 work-items or more, which the runtime refuses.

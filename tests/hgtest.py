@@ -2,6 +2,8 @@
 oracle on the same seeded BF16 bytes and compare their outputs."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -97,3 +99,27 @@ def compare_full(w, K, V, mask, stream=None, prefill=None):
     rep["K_exact"] = bool(np.array_equal(g_K, o_K))
     rep["V_exact"] = bool(np.array_equal(g_V, o_V))
     return rep
+
+
+# Host-only queries of the rules that choose a call's kernels.
+
+def select_with_values(slices, n, D, bits):
+    """The selection of a quantize call with retention runs among the value tiles."""
+    import paper_2609_35800_amd as hg
+    f = hg.library().hg_test_select_with_values
+    f.argtypes, f.restype = [C.c_uint64, C.c_uint64, C.c_int, C.c_int], C.c_int
+    return bool(f(slices, n, D, bits))
+
+
+SPLIT, GROUPS, SPREAD = 2, 1, 3
+
+
+def kivi_plan(T, D, items, n=None, cus=256):
+    """(kind, partners, row slots, groups, workspace words, polls) of a call with
+    whole-sequence keys."""
+    import paper_2609_35800_amd as hg
+    out = (C.c_uint32 * 6)()
+    f = hg.library().hg_test_kivi_plan
+    f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_uint32 * 6], None
+    f(T, T - 800 if n is None else n, D, items, cus, out)
+    return tuple(out)

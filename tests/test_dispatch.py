@@ -6,14 +6,9 @@ import random
 import pytest
 
 import paper_2609_35800_amd as hg
+from hgtest import GROUPS, SPLIT, SPREAD, kivi_plan, select_with_values
 
 THREADS, BLOCK_TOKENS = 256, 128  # a workgroup of the quantize kernels
-
-
-def select_with_values(slices, n, D, bits):
-    f = hg.library().hg_test_select_with_values
-    f.argtypes, f.restype = [C.c_uint64, C.c_uint64, C.c_int, C.c_int], C.c_int
-    return bool(f(slices, n, D, bits))
 
 
 @pytest.mark.parametrize("n", [1, 128, 129, 1000])
@@ -25,6 +20,19 @@ def test_selection_with_the_values_stays_under_the_launch_limit(n, D):
     most = (2**32 - 1) // THREADS // per_slice
     assert select_with_values(most, n, D, 2) and not select_with_values(most + 1, n, D, 2)
     assert not select_with_values(2**23, n, D, 2) or 2**23 * per_slice * THREADS < 2**32
+
+
+# Spans whose norms fit the LDS that the value tiles' occupancy leaves: 160 KiB over
+# one workgroup more than stay per compute unit (6 at 2 bits, 5 at 3, 4 at 4 bits and
+# at head_dim 256) and 512 bytes, less the selection's 1072 and, at head_dim 256, the
+# staged loads' 16 KiB.
+@pytest.mark.parametrize("D,bits,limit", [(64, 2, 5711), (128, 2, 5711), (128, 3, 6686), (128, 4, 8052),
+                                          (256, 2, 3956), (256, 3, 3956), (256, 4, 3956)])
+def test_longest_span_selected_among_the_values(D, bits, limit):
+    waves = 4 if bits == 4 or D == 256 else 5 if bits == 3 else 6
+    lds = 160 * 1024 // (waves + 1) + 512 - 1072 - (16384 if D == 256 else 0)
+    assert limit == lds // 4
+    assert select_with_values(8, limit, D, bits) and not select_with_values(8, limit + 1, D, bits)
 
 
 @pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 6, 7, 10, 11, 20, 21, 26, 31, 54, 55, 63])
@@ -55,19 +63,6 @@ def test_retained_rows_in_the_dequantize_kernel(D, n, k, slices, fused):
     f = hg.library().hg_test_retain_in_dequantize
     f.argtypes, f.restype = [C.c_uint64, C.c_int64, C.c_int64, C.c_int], C.c_int
     assert bool(f(4 * slices * n * D, n, k, D)) == fused
-
-
-SPLIT, GROUPS, SPREAD = 2, 1, 3
-
-
-def kivi_plan(T, D, items, n=None, cus=256):
-    """(kind, partners, row slots, groups, workspace words, polls) of a call with
-    whole-sequence keys."""
-    out = (C.c_uint32 * 6)()
-    f = hg.library().hg_test_kivi_plan
-    f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_uint32, C.c_int, C.c_uint32 * 6], None
-    f(T, T - 800 if n is None else n, D, items, cus, out)
-    return tuple(out)
 
 
 # Slices past 32 workgroups' rows: spread groups or the split kernels, whichever was

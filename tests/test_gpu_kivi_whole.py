@@ -24,7 +24,7 @@ import torch
 
 import synthkv
 import wholecache
-from hgtest import compare_full
+from hgtest import GROUPS, compare_full, kivi_plan
 from test_gpu_fakequant import check as check_fake
 from test_gpu_parity import _assert_exact, small
 
@@ -203,6 +203,29 @@ def test_form_boundary(D, cus, T, monkeypatch):
     K[0, :, :, T - 1, 5] = -4000.0  # extremes in the last and first rows
     K[0, :, :, 0, 9] = 5000.0
     _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), f"D{D}-T{T}-cus{cus}")
+
+
+# Each form filled to the last row slot, with the partners and slots that the plan
+# takes there: one workgroup, groups of up to 8 and wide groups (24 slices).
+FORM_CAPACITY = [("", 1, 8), ("", 1, 15), ("", 8, 8), ("", 6, 15), ("", 8, 15), ("", 8, 24), ("", 16, 15), ("", 16, 24),
+                 ("64", 2, 15), ("64", 2, 24)]
+
+
+@pytest.mark.parametrize("D,inplace", [(64, None), (128, None), (256, None), (128, True)])
+@pytest.mark.parametrize("cus,P,slots", FORM_CAPACITY, ids=lambda v: str(v) or "all")
+def test_form_capacity(D, cus, P, slots, inplace, monkeypatch):
+    monkeypatch.setenv("HG_TEST_CUS", cus)
+    T = P * slots * 8192 // D
+    w = small("kivi", D, 2, 1, img_len=T - 9, img_start=4, text=5, L=2, B=3, H=5,
+              n_protected=2).with_(kivi_group=0, name=f"kiviseq-form-D{D}-P{P}-{slots}")
+    assert kivi_plan(w.T, D, 24, w.img_len, int(cus or 256))[:3] == (GROUPS, P, slots)
+    K, V = synthkv.gen_kv(w)
+    K[0, :, :, T - 1, 5] = -4000.0  # extremes in the last and first rows
+    K[0, :, :, 0, 9] = 5000.0
+    if inplace is None:
+        _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), w.name)
+    else:
+        check_fake(w, K, V, synthkv.protect_mask(w), inplace)
 
 
 @pytest.mark.parametrize("T", [1536, 1537, 3008, 12288, 12289, 24577, 49152, 49153])

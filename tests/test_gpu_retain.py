@@ -17,7 +17,7 @@ import torch
 
 import synthkv
 import wholecache
-from hgtest import compare_full
+from hgtest import compare_full, select_with_values
 from test_gpu_fakequant import check as check_fake
 from test_gpu_parity import _assert_exact, _special_values, small
 
@@ -70,6 +70,18 @@ def test_route_boundaries(D, img_len, permille):
                         permille=permille)
         K, V = synthkv.gen_kv(w)
         _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), w.name)
+
+
+# The longest span whose norms fit the launch of the values, filled to the last
+# word, and one token more.
+@pytest.mark.parametrize("D,bits,limit", [(128, 2, 5711), (64, 3, 6686), (128, 4, 8052), (256, 2, 3956), (256, 4, 3956)])
+@pytest.mark.parametrize("past", [0, 1])
+def test_selection_limits(D, bits, limit, past):
+    w = retain_case(D=D, bits=bits, img_len=limit + past, img_start=5, text=3, L=1, B=1, H=3, n_protected=1)
+    assert select_with_values(3, w.img_len, D, bits) == (not past)
+    K, V = synthkv.gen_kv(w)
+    K[..., 5 + w.img_len - 1, :] = 50.0  # the last token has the largest norm
+    _assert_exact(compare_full(w, K, V, synthkv.protect_mask(w)), w.name)
 
 
 def test_list_in_any_order():
