@@ -5,7 +5,7 @@
 //
 // Every code depends on the range of its channel over all T rows of the
 // slice, so a slice must be fully read before any of its codes is formed.
-// Three forms:
+// Four ways:
 //
 // Partitioned resident kernel (T at most 32 workgroups' capacity; more below): a
 // persistent grid of 1024-thread workgroups, one per compute unit.  A group of
@@ -49,11 +49,12 @@
 // roll call before it that hands the call to the split kernels if some
 // workgroup of the grid is not on the chip.
 //
-// Split kernels (longer slices, too few compute units for a group of eight, or
-// a spread launch that found workgroups missing): a range launch over chunks of every slice, whose per-channel ranges
-// are merged into the workspace by atomic maxima, then a code launch over
-// chunks of the image rows; each slice is read twice, but every compute unit
-// works on it.
+// Split kernels (longer slices, too few compute units for a group of eight, a
+// spread launch that found workgroups missing, or sizes where they are faster
+// than spread groups): a range launch over chunks of every slice, whose
+// per-channel ranges are merged into the workspace by atomic maxima, then a code
+// launch over chunks of the image rows; each slice is read twice, but every
+// compute unit works on it.
 //
 // Two-pass kernel (a slice one workgroup holds, with no workspace, on a
 // device of fewer than 8 compute units): a persistent grid of
@@ -1088,9 +1089,9 @@ static KiviPlan plan_rows(int T, int n, int D, uint32_t n_items, bool has_ws, in
   // round (one slice per group) takes its rows at the chip's rate, or a
   // workgroup's own at 20/11 of its share if that is longer, a third of the
   // empty slots (they load the last row again) and the exchange, three slots.
-  // Measured (2-bit keys at head_dim 128, T = 3000, whole
-  // calls): 28 slices in place, 2 workgroups of the longest form 30.1 us, 8 of
-  // it 30.3, 8 of the shortest 22.0; 56 slices, 2 of the longest 35.0, 4 of the
+  // Measured (2-bit keys at head_dim 128, T = 3000, whole calls, without the
+  // partners' agreement, 0.3 to 0.6 us): 28 slices in place, 2 workgroups of the longest form 30.1 us, 8 of
+  // it 30.3, 8 of the shortest 22.6; 56 slices, 2 of the longest 35.0, 4 of the
   // middle one 31.2, 6 of the shortest (two rounds) 34.3; 280 slices, 2 of the
   // longest 111.6, 4 of the middle one 113.2, 6 of the shortest 115.5; 3584
   // slices (3 bits) 1346, 1400 and 1501.  So more workgroups of a shorter form

@@ -16,8 +16,10 @@ workspace, then a code launch), and a slice one workgroup holds, on a device
 too small for a group, through the two-pass kernel (no workspace).
 Covered: one to eight, 16 and 32 workgroups per slice and the capacity
 boundaries, several slices per group (with the grid shrunk through the
-HG_TEST_CUS hook), identical bytes for different grid sizes, and no exchange
-wait running out of polls."""
+HG_TEST_CUS hook), identical bytes for different grid sizes, no exchange
+wait running out of polls, and groups some of whose partners do not run or
+come late (HG_TEST_ABSENT, HG_TEST_POLLS), whose slices the others then take
+one workgroup a slice."""
 import numpy as np
 import pytest
 import torch
