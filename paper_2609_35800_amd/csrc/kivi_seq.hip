@@ -241,9 +241,10 @@ constexpr int kPartWaves = kPartThreads / 64;
 // Row slots of a workgroup, in registers and in LDS, by form (16 bytes a
 // thread and slot).  The longest form holds the most rows and streams whole
 // caches, the last one (16 slots) serves spread groups; the shorter ones issue and
-// wait for fewer loads where a workgroup
-// has fewer rows (testing each slot's use instead made every wait a full one,
-// 1346 -> 1440 us on 3584 slices of 3008 rows).
+// wait for fewer loads where a workgroup has fewer rows (testing each slot's use
+// instead made every wait a full one, 1346 -> 1440 us on 3584 slices of 3008 rows).
+// The one-pass kernels of the forms with 15 register slots spill 5 to 10 registers
+// (24 to 44 bytes of scratch a lane).
 constexpr int kPartForms = 4;
 constexpr int kPartRegSlots[kPartForms] = {15, 15, 8, 15};
 constexpr int kPartLdsSlots[kPartForms] = {9, 0, 0, 1};
